@@ -441,6 +441,34 @@ __device__ inline float col_sum(float s) {
   return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
+// Column layout -> natural layout (register r of lane group g: feature 4 r +
+// g): a 4 x 4 transposition of registers and lane groups per 16 features.
+__device__ inline void swap32(float& a, float& b) {
+  const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(x[0]);
+  b = __uint_as_float(x[1]);
+}
+__device__ inline void swap16(float& a, float& b) {
+  const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(x[0]);
+  b = __uint_as_float(x[1]);
+}
+template <int F>
+__device__ inline void to_nat(float* n, const float* c) {
+#pragma unroll
+  for (int q = 0; q < F / 4; q += 4) {
+    float a = c[q], b = c[q + 1], d = c[q + 2], e = c[q + 3];
+    swap32(a, d);
+    swap32(b, e);
+    swap16(a, b);
+    swap16(d, e);
+    n[q] = a;
+    n[q + 1] = b;
+    n[q + 2] = d;
+    n[q + 3] = e;
+  }
+}
+
 // LayerNorm over the F features of each column (biased variance, eps 1e-5,
 // no affine), then ReLU.  Two passes (mean, then squared deviations); the
 // reciprocal square root is the hardware's (1 ulp; its argument is at least

@@ -1,314 +1,268 @@
-// In-library training of the embedding MLP and the interaction network
-// (thesis ch. 8 "Hit Embedding and Rough Graph Construction", eqs. loss1-loss3,
-// and "Graph Neural Network and Classifiers", eq. gnn-loss without the triplet
-// term): forward passes that keep what the backward needs, reverse-mode
-// gradients layer by layer, and Adam on FP32 master parameters.
+// In-library training of the embedding MLP (thesis ch. 8 "Hit Embedding and
+// Rough Graph Construction", eqs. loss1-loss3): the forward that keeps what
+// the backward needs, the pairwise hinge loss, and the backward with its
+// weight gradients.
 //
-// Every layer is a row-wise kernel: one thread per row (a hit or an edge)
-// holds the row's outputs in registers, reads its input from up to three
-// segments (each a row of a node or edge buffer, directly or through a
-// source / target index), and takes the layer's weights from LDS.  The weight
-// gradients are sums over rows: every chunk of rows adds its rows in order
-// into a partial, and the partials are added in chunk order, so a training
-// step is bitwise reproducible.  The transpose of a gather by source (target)
-// is a sum over the node's out-edges (in-edges), taken through the CSR rows
-// (the CSC permutation); the transpose of the out-/in-sums is a gather.
-#include <cmath>
-
+// The forward builds the training graph, whose edges are decided by single
+// bits of the embedding, so every output is one chain of multiply-adds over
+// its inputs in order, starting from the bias.  The backward is products on
+// the FP32 matrix cores in the column layout of tile.hpp; weight gradients are
+// one partial per workgroup, added in a fixed order by the parameter update
+// (train_net.hip), so a step is bitwise reproducible.
 #include "internal.hpp"
+#include "tile.hpp"
 #include "train.hpp"
 
 namespace etx {
 
 namespace {
 
-constexpr int kRowThreads = 128;
-constexpr int kWgradThreads = 256;
+constexpr int kThreads = 256;
 
-__device__ inline float seg_x(const TrainSeg& s, int64_t r, int k) {
-  const int64_t row = s.idx ? (int64_t)s.idx[r] : r;
-  return s.base[row * s.ld + k];
+// Sixteen hits per workgroup, sixteen threads per hit: a thread holds W / 16
+// outputs of its hit, the hit's inputs are read from LDS (broadcast within the
+// row's threads), the layer's weights from LDS in 16-byte chunks.  All layers
+// of the 16 hits run in one launch; a one-event batch (about 1,800 hits) fills
+// 114 workgroups.
+constexpr int kEmbRows = 16;
+
+template <int N>
+__device__ inline void fma_row(float* z, float x, const float* w) {
+#pragma unroll
+  for (int m = 0; m < N; ++m) z[m] = fmaf(x, w[m], z[m]);
 }
 
-// y = act(x W + b) per row; ACT 0 none, 1 ReLU, 2 LayerNorm (no affine,
-// biased variance, eps 1e-5) then ReLU.  yhat keeps z (ACT 0, 1) or the
-// normalised value before the ReLU (ACT 2); rstd its reciprocal standard
-// deviation (ACT 2).  resid (optional): y = resid + act(...).
-template <int M, int ACT>
-__global__ __launch_bounds__(kRowThreads) void k_blk_fwd(BlkFwd A) {
+template <int W>
+__global__ __launch_bounds__(kThreads) void k_emb_fwd(EmbTrain A, int L) {
   if (A.status[0] != 0) return;
-  extern __shared__ float w[];
-  const int K = A.K;
-  for (int i = threadIdx.x; i < K * M + M; i += blockDim.x) w[i] = A.W[i];
-  __syncthreads();
-  const float* b = w + K * M;
-  for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < A.rows; r += (int64_t)gridDim.x * blockDim.x) {
-    float z[M];
+  constexpr int N = W / 16;                // outputs per thread
+  constexpr int LDX = W + 4;
+  extern __shared__ __align__(16) float lds[];
+  float* w = lds;                          // [W][W]
+  float* xs = w + W * W;                   // [2][kEmbRows][LDX]
+  const int r = threadIdx.x >> 4, c = threadIdx.x & 15;
+  for (int64_t t0 = (int64_t)blockIdx.x * kEmbRows; t0 < A.n; t0 += (int64_t)gridDim.x * kEmbRows) {
+    const int64_t row = t0 + r;
+    const bool valid = row < A.n;
+    const int64_t i = valid ? row : A.n - 1;
+    float in[3];
+    in[0] = hypotf(A.x[i], A.y[i]) * A.inv_r;
+    in[1] = atan2f(A.y[i], A.x[i]) * (1.0f / 3.14159265358979f);
+    in[2] = A.z[i] * A.inv_z;
+    float z[N];
+    // layer 0: output m = c N + q
+    {
+      const float* W0 = A.W[0];
 #pragma unroll
-    for (int m = 0; m < M; ++m) z[m] = b[m];
-    int ko = 0;
-    for (int s = 0; s < A.nseg; ++s) {
-      const TrainSeg& g = A.seg[s];
-      const int64_t row = g.idx ? (int64_t)g.idx[r] : r;
-      const float* x = g.base + row * g.ld;
-      for (int k = 0; k < g.width; ++k) {
-        const float xv = x[k];
-        const float* wk = w + (ko + k) * M;
+      for (int q = 0; q < N; ++q) z[q] = W0[3 * W + c * N + q];
 #pragma unroll
-        for (int m = 0; m < M; ++m) z[m] = fmaf(xv, wk[m], z[m]);
-      }
-      ko += g.width;
+      for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int q = 0; q < N; ++q) z[q] = fmaf(in[k], W0[k * W + c * N + q], z[q]);
     }
-    float* yh = A.yhat ? A.yhat + r * M : nullptr;
-    float* y = A.y + r * A.ldy;
-    const float* res = A.resid ? A.resid + r * A.ldy : nullptr;
-    if (ACT == 2) {
-      float mean = 0.f;
+    for (int l = 0; l < L; ++l) {
+      float* xb = xs + (l & 1) * kEmbRows * LDX + r * LDX;
 #pragma unroll
-      for (int m = 0; m < M; ++m) mean += z[m];
-      mean *= 1.0f / M;
-      float var = 0.f;
-#pragma unroll
-      for (int m = 0; m < M; ++m) var = fmaf(z[m] - mean, z[m] - mean, var);
-      const float rs = 1.0f / sqrtf(var * (1.0f / M) + 1e-5f);
-      A.rstd[r] = rs;
-#pragma unroll
-      for (int m = 0; m < M; ++m) {
-        const float t = (z[m] - mean) * rs;
-        if (yh) yh[m] = t;
-        const float v = fmaxf(t, 0.f);
-        y[m] = res ? res[m] + v : v;
+      for (int q = 0; q < N; ++q) {
+        if (valid) A.zs[l][row * W + c * N + q] = z[q];
+        xb[c * N + q] = fmaxf(z[q], 0.f);
       }
-    } else {
+      const float* Wn = A.W[l + 1];
+      if (l + 1 < L) {
+#pragma unroll 8
+        for (int k = threadIdx.x; k < W * W; k += kThreads) w[k] = Wn[k];
+        __syncthreads();
 #pragma unroll
-      for (int m = 0; m < M; ++m) {
-        if (yh) yh[m] = z[m];
-        const float v = ACT == 1 ? fmaxf(z[m], 0.f) : z[m];
-        y[m] = res ? res[m] + v : v;
+        for (int q = 0; q < N; ++q) z[q] = Wn[W * W + c * N + q];
+#pragma unroll 8
+        for (int k = 0; k < W; ++k) fma_row<N>(z, xb[k], w + k * W + c * N);
+      } else {
+        for (int k = threadIdx.x; k < W * A.D; k += kThreads) w[k] = Wn[k];
+        __syncthreads();
+        float o = 0.f;
+        if (c < A.D) {
+          o = Wn[W * A.D + c];
+#pragma unroll 8
+          for (int k = 0; k < W; ++k) o = fmaf(xb[k], w[k * A.D + c], o);
+        }
+        if (valid) A.emb[row * kDpad + c] = o;
       }
+      __syncthreads();                     // the next layer's (or tile's) weights replace these
     }
-    for (int m = M; m < A.ldy && A.pad_zero; ++m) y[m] = 0.f;
   }
 }
 
-// dz = d(act)/dz applied to dy (+ dy2); dx = W dz into the input segments'
-// gradient buffers (written, or added to, per segment).
-template <int M, int ACT>
-__global__ __launch_bounds__(kRowThreads) void k_blk_bwd(BlkBwd A) {
+// Backward: one chunk of hits per workgroup (see train_net.hip: chunks, order
+// of additions, natural layout), layer by layer from the output; the layer's
+// dL/dz goes through one LDS buffer for its weight gradient, its weights
+// replace the previous layer's.
+constexpr int kRows = 64;
+
+template <int W, int L>
+__global__ __launch_bounds__(kThreads) void k_emb_bwd(EmbTrain A) {
   if (A.status[0] != 0) return;
-  extern __shared__ float w[];
-  const int K = A.K;
-  for (int i = threadIdx.x; i < K * M; i += blockDim.x) w[i] = A.W[i];
-  __syncthreads();
-  for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < A.rows; r += (int64_t)gridDim.x * blockDim.x) {
-    float dz[M];
-    const float* dy = A.dy + r * A.lddy;
-    const float* dy2 = A.dy2 ? A.dy2 + r * A.lddy : nullptr;
-    const float* yh = A.yhat + r * M;
+  constexpr int LD = W + 4, LDZ = W + 16, LDO = 16 + 4, NI = (W / 16 + 3) / 4, MB = W / 16;
+  constexpr int NIN = (3 * W + kThreads - 1) / kThreads;
+  extern __shared__ __align__(16) float lds[];
+  float* w = lds;                          // [W][LD] (the output layer: [W][LDO], columns past D zero)
+  float* zb = w + W * LD;                  // [kRows][LDZ] (the output layer: [kRows][LDO])
+  float* cyl = zb + kRows * LDZ;           // [3][kRows]
+  const int lane = lane_id(), g = lane_group(), j = lane & 15, wave = wave_id(), t = threadIdx.x;
+  const int local = wave * kCols + j;
+  floatx4 acc_o[NI], acc_h[L > 1 ? L - 1 : 1][NI][MB];
+  float bias[L + 1], in_acc[NIN];
 #pragma unroll
-    for (int m = 0; m < M; ++m) dz[m] = dy2 ? dy[m] + dy2[m] : dy[m];
-    if (ACT == 2) {
-      float mg = 0.f, mgy = 0.f;
+  for (int i = 0; i < NI; ++i) {
+    acc_o[i] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int m = 0; m < M; ++m) {
-        dz[m] = yh[m] > 0.f ? dz[m] : 0.f;
-        mg += dz[m];
-        mgy = fmaf(dz[m], yh[m], mgy);
-      }
-      mg *= 1.0f / M;
-      mgy *= 1.0f / M;
-      const float rs = A.rstd[r];
+    for (int l = 0; l < L - 1; ++l)
 #pragma unroll
-      for (int m = 0; m < M; ++m) dz[m] = rs * (dz[m] - mg - yh[m] * mgy);
-    } else if (ACT == 1) {
+      for (int mb = 0; mb < MB; ++mb) acc_h[l][i][mb] = floatx4{0.f, 0.f, 0.f, 0.f};
+  }
 #pragma unroll
-      for (int m = 0; m < M; ++m) dz[m] = yh[m] > 0.f ? dz[m] : 0.f;
+  for (int l = 0; l <= L; ++l) bias[l] = 0.f;
+#pragma unroll
+  for (float& v : in_acc) v = 0.f;
+  const int64_t per = (A.n + kTrainChunks - 1) / kTrainChunks;
+  const int64_t begin = (int64_t)blockIdx.x * per, end = min(begin + per, A.n);
+  for (int64_t t0 = begin; t0 < end; t0 += kRows) {
+    const int nr = (int)min((int64_t)kRows, end - t0);
+    const bool live = wave * kCols < nr;
+    const int64_t row = t0 + local;
+    const bool valid = row < end;
+    const int64_t r = valid ? row : end - 1;
+    if (g == 0) {
+      cyl[local] = hypotf(A.x[r], A.y[r]) * A.inv_r;
+      cyl[kRows + local] = atan2f(A.y[r], A.x[r]) * (1.0f / 3.14159265358979f);
+      cyl[2 * kRows + local] = A.z[r] * A.inv_z;
     }
-    float* dzo = A.dz + r * M;
+    // the input of layer l's weight gradient: the lane's feature of a local row
+    auto x_of = [&](int l, int kb, int q) {
+      return fmaxf(A.zs[l - 1][min(t0 + q, end - 1) * W + 16 * kb + j], 0.f);
+    };
+    // output layer
+    float dz[MB * 4], dn[MB * 4];          // column and natural layout
+    {
+      const float* Wo = A.W[L];
+      for (int i = t; i < W * 16; i += kThreads) w[(i / 16) * LDO + i % 16] = i % 16 < A.D ? Wo[(i / 16) * A.D + i % 16] : 0.f;
+      float d[4];
 #pragma unroll
-    for (int m = 0; m < M; ++m) dzo[m] = dz[m];
-    int ko = 0;
-    for (int s = 0; s < A.nseg; ++s) {
-      const TrainOut& o = A.out[s];
-      if (o.base) {
-        float* dx = o.base + r * o.ld;
-        for (int k = 0; k < o.width; ++k) {
-          const float* wk = w + (ko + k) * M;
-          float v = 0.f;
+      for (int v = 0; v < 4; ++v) d[v] = valid && 4 * g + v < A.D ? A.de[r * kDpad + 4 * g + v] : 0.f;
+      *reinterpret_cast<float4*>(zb + local * LDO + 4 * g) = make_float4(d[0], d[1], d[2], d[3]);
+      __syncthreads();
 #pragma unroll
-          for (int m = 0; m < M; ++m) v = fmaf(wk[m], dz[m], v);
-          dx[k] = o.add ? dx[k] + v : v;
+      for (int i = 0; i < NI; ++i) {
+        const int kb = wave + 4 * i;
+        if (kb < MB)
+          for (int q0 = 0; q0 < nr; q0 += 4) {
+            const int q = q0 + g;
+            acc_o[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(x_of(L, kb, q), zb[q * LDO + j], acc_o[i], 0, 0, 0);
+          }
+      }
+      if (t < 16)
+        for (int q = 0; q < nr; ++q) bias[L] += zb[q * LDO + t];
+      if (live) {
+        to_nat<16>(d, d);
+#pragma unroll
+        for (int kb = 0; kb < MB; ++kb) {
+          floatx4 c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+            c = __builtin_amdgcn_mfma_f32_16x16x4f32(w[(16 * kb + j) * LDO + 4 * s + g], d[s], c, 0, 0, 0);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) dz[4 * kb + v] = c[v];
         }
       }
-      ko += o.width;
+      __syncthreads();
+    }
+    // hidden layers, through the ReLU of each
+#pragma unroll
+    for (int l = L - 1; l >= 0; --l) {
+      if (live) {
+        float z[MB * 4];
+        load_cols<W>(z, A.zs[l] + r * W, true);
+#pragma unroll
+        for (int q = 0; q < MB * 4; ++q) dz[q] = valid && z[q] > 0.f ? dz[q] : 0.f;
+#pragma unroll
+        for (int c = 0; c < MB; ++c)
+          *reinterpret_cast<float4*>(zb + local * LDZ + 16 * c + 4 * g) =
+              make_float4(dz[4 * c], dz[4 * c + 1], dz[4 * c + 2], dz[4 * c + 3]);
+      }
+      if (l > 0) {
+        const float* Wl = A.W[l];
+#pragma unroll 8
+        for (int i = t; i < W * W; i += kThreads) w[(i / W) * LD + i % W] = Wl[i];
+      }
+      __syncthreads();
+      if (t < W) {
+#pragma unroll 8
+        for (int q = 0; q < nr; ++q) bias[l] += zb[q * LDZ + t];
+      }
+      if (l > 0) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+          const int kb = wave + 4 * i;
+          if (kb < MB)
+            for (int q0 = 0; q0 < nr; q0 += 4) {
+              const int q = q0 + g;
+              const float x = x_of(l, kb, q);
+#pragma unroll
+              for (int mb = 0; mb < MB; ++mb)
+                acc_h[l - 1][i][mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, zb[q * LDZ + 16 * mb + j],
+                                                                           acc_h[l - 1][i][mb], 0, 0, 0);
+            }
+        }
+        if (live) {
+          to_nat<W>(dn, dz);
+          floatx4 c[MB];
+#pragma unroll
+          for (int kb = 0; kb < MB; ++kb) c[kb] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int s = 0; s < MB * 4; ++s)
+#pragma unroll
+            for (int kb = 0; kb < MB; ++kb)
+              c[kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[(16 * kb + j) * LD + 4 * s + g], dn[s], c[kb], 0, 0, 0);
+#pragma unroll
+          for (int kb = 0; kb < MB; ++kb)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) dz[4 * kb + v] = c[kb][v];
+        }
+      } else {
+#pragma unroll
+        for (int u = 0; u < NIN; ++u) {
+          const int o = t + u * kThreads;
+          if (o < 3 * W) {
+            const float* x = cyl + (o / W) * kRows;
+#pragma unroll 8
+            for (int q = 0; q < nr; ++q) in_acc[u] = fmaf(x[q], zb[q * LDZ + o % W], in_acc[u]);
+          }
+        }
+      }
+      __syncthreads();
     }
   }
-}
-
-// weight gradient partials: chunk c adds, row by row in order, x_r[k] dz_r[m]
-// (and dz_r[m] for the bias) over its rows; one thread per output
-template <int M>
-__global__ __launch_bounds__(kWgradThreads) void k_wgrad(Wgrad A) {
-  if (A.status[0] != 0) return;
-  const int K = A.K;
-  const int n_out = K * M + M;
-  const int o = blockIdx.y * blockDim.x + threadIdx.x;
-  if (o >= n_out) return;
-  const int64_t per = (A.rows + gridDim.x - 1) / gridDim.x;
-  const int64_t r0 = (int64_t)blockIdx.x * per, r1 = r0 + per < A.rows ? r0 + per : A.rows;
-  float acc = 0.f;
-  if (o < K * M) {
-    const int k = o / M, m = o % M;
-    // the segment holding input feature k
-    int s = 0, kk = k;
-    while (kk >= A.seg[s].width) kk -= A.seg[s++].width;
-    const TrainSeg g = A.seg[s];
-    for (int64_t r = r0; r < r1; ++r) acc = fmaf(seg_x(g, r, kk), A.dz[r * M + m], acc);
-  } else {
-    const int m = o - K * M;
-    for (int64_t r = r0; r < r1; ++r) acc += A.dz[r * M + m];
-  }
-  A.partial[(int64_t)blockIdx.x * n_out + o] = acc;
-}
-
-// grad[o] (+)= sum of the chunk partials in chunk order
-__global__ void k_reduce_partials(const float* __restrict__ partial, int n_chunks, int n_out, float* __restrict__ grad,
-                                  const int64_t* status) {
-  if (status[0] != 0) return;
-  const int o = blockIdx.x * blockDim.x + threadIdx.x;
-  if (o >= n_out) return;
-  float s = 0.f;
-  for (int c = 0; c < n_chunks; ++c) s += partial[(int64_t)c * n_out + o];
-  grad[o] = s;
-}
-
-// out[l] (+)= sum over l's out-edges (CSR rows, in edge order) of a[t], plus
-// the sum over its in-edges (CSC permutation, in CSC order) of b[t]
-__global__ void k_node_sum(int64_t n, int H, const int64_t* __restrict__ row_ptr, const float* __restrict__ a,
-                           const int64_t* __restrict__ col_ptr, const int32_t* __restrict__ csc,
-                           const float* __restrict__ b, float* __restrict__ out, int add, const int64_t* status) {
-  if (status[0] != 0) return;
-  const int64_t total = n * H;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t l = i / H;
-    const int f = (int)(i % H);
-    float s = add ? out[i] : 0.f;
-    if (a)
-      for (int64_t t = row_ptr[l]; t < row_ptr[l + 1]; ++t) s += a[t * H + f];
-    if (b)
-      for (int64_t q = col_ptr[l]; q < col_ptr[l + 1]; ++q) s += b[(int64_t)csc[q] * H + f];
-    out[i] = s;
-  }
-}
-
-// out[t] += A[src[t]] + B[dst[t]]
-__global__ void k_edge_gather_add(int64_t E, int H, const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
-                                  const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ out,
-                                  const int64_t* status) {
-  if (status[0] != 0) return;
-  const int64_t total = E * H;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t t = i / H;
-    const int f = (int)(i % H);
-    out[i] += A[(int64_t)src[t] * H + f] + B[(int64_t)dst[t] * H + f];
-  }
-}
-
-// the network's inputs: normalised Cartesian (x/R, y/R, z/Z) per hit
-__global__ void k_cart(int64_t n, const float* x, const float* y, const float* z, float inv_r, float inv_z,
-                       float* __restrict__ cart, const int64_t* status) {
-  if (status[0] != 0) return;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    cart[3 * i] = x[i] * inv_r;
-    cart[3 * i + 1] = y[i] * inv_r;
-    cart[3 * i + 2] = z[i] * inv_z;
-  }
-}
-
-// the embedding's inputs: (r/R, phi/pi, z/Z) per hit
-__global__ void k_cyl(int64_t n, const float* x, const float* y, const float* z, float inv_r, float inv_z,
-                      float* __restrict__ cyl, const int64_t* status) {
-  if (status[0] != 0) return;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    cyl[3 * i] = hypotf(x[i], y[i]) * inv_r;
-    cyl[3 * i + 1] = atan2f(y[i], x[i]) * (1.0f / 3.14159265358979f);
-    cyl[3 * i + 2] = z[i] * inv_z;
-  }
-}
-
-// an edge is genuine when its target is the source's successor on one of its particles
-__global__ void k_edge_labels(int64_t E, const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
-                              const int32_t* __restrict__ succ, const int32_t* __restrict__ succ2,
-                              uint8_t* __restrict__ lab, const int64_t* status) {
-  if (status[0] != 0) return;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < E; t += (int64_t)gridDim.x * blockDim.x)
-    lab[t] = (succ[src[t]] == dst[t] || (succ2 && succ2[src[t]] == dst[t])) ? 1 : 0;
-}
-
-// Sigmoid focal loss of every edge (Lin et al.): logit z = c w2 + b2; per-edge
-// dL/dz / E into dlogit, dL/dc = w2 dlogit into dc, and the loss per block.
-__global__ __launch_bounds__(256) void k_focal(int64_t E, int H, const float* __restrict__ c,
-                                               const float* __restrict__ w2, const uint8_t* __restrict__ lab,
-                                               float alpha, float gamma, float* __restrict__ dlogit,
-                                               float* __restrict__ dc, float* __restrict__ loss_part,
-                                               float* __restrict__ score, const int64_t* status) {
-  if (status[0] != 0) return;
-  __shared__ float part[256];
-  float acc = 0.f;
-  const float inv_e = E > 0 ? 1.0f / (float)E : 0.f;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < E; t += (int64_t)gridDim.x * blockDim.x) {
-    float z = w2[H];
-    for (int q = 0; q < H; ++q) z = fmaf(c[t * H + q], w2[q], z);
-    const float p = 1.0f / (1.0f + expf(-z));
-    if (score) score[t] = p;
-    const float lp = -(z < 0.f ? -z + log1pf(expf(z)) : log1pf(expf(-z)));     // log p
-    const float l1p = -(z > 0.f ? z + log1pf(expf(-z)) : log1pf(expf(z)));     // log (1 - p)
-    float l, d;
-    if (lab[t]) {
-      const float wt = powf(1.f - p, gamma);
-      l = -alpha * wt * lp;
-      d = alpha * wt * (gamma * p * lp - (1.f - p));
-    } else {
-      const float wt = powf(p, gamma);
-      l = -(1.f - alpha) * wt * l1p;
-      d = (1.f - alpha) * wt * (p - gamma * (1.f - p) * l1p);
+  float* part = A.part + (int64_t)blockIdx.x * A.part_stride;
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int kb = wave + 4 * i;
+    if (kb >= MB) continue;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int k = 16 * kb + 4 * g + v;
+      if (j < A.D) part[A.o[L] + k * A.D + j] = acc_o[i][v];
+#pragma unroll
+      for (int l = 1; l < L; ++l)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) part[A.o[l] + k * W + 16 * mb + j] = acc_h[l - 1][i][mb][v];
     }
-    acc += l;
-    d *= inv_e;
-    dlogit[t] = d;
-    for (int q = 0; q < H; ++q) dc[t * H + q] = w2[q] * d;
   }
-  part[threadIdx.x] = acc;
-  __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s) part[threadIdx.x] += part[threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) loss_part[blockIdx.x] = part[0] * inv_e;
-}
-
-// loss = sum of the block partials in block order
-__global__ void k_sum(const float* __restrict__ part, int n, float* __restrict__ out, int slot, const int64_t* status) {
-  if (status[0] != 0) return;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    float s = 0.f;
-    for (int i = 0; i < n; ++i) s += part[i];
-    out[slot] = s;
-  }
-}
-
-__global__ void k_adam(int64_t n, float* __restrict__ p, float* __restrict__ m, float* __restrict__ v,
-                       const float* __restrict__ g, float lr, float b1, float b2, float eps, float c1, float c2,
-                       const int64_t* status) {
-  if (status[0] != 0) return;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.f - b1) * gi;
-    const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-  }
+#pragma unroll
+  for (int u = 0; u < NIN; ++u)
+    if (t + u * kThreads < 3 * W) part[A.o[0] + t + u * kThreads] = in_acc[u];
+#pragma unroll
+  for (int l = 0; l < L; ++l)
+    if (t < W) part[A.o[l] + (l == 0 ? 3 : W) * W + t] = bias[l];
+  if (t < A.D) part[A.o[L] + W * A.D + t] = bias[L];
 }
 
 // ---------------------------------------------------------------------------
@@ -319,19 +273,37 @@ __global__ void k_adam(int64_t n, float* __restrict__ p, float* __restrict__ m, 
 // genuine pair (q, succ[q]); fake pairs: its hard negatives (the targets of
 // the training radius graph that belong to a particle and are not succ[q])
 // and its random pair (q, rnd[q]) unless that is succ[q].  Pass 0 counts them
-// per block; pass 1 writes, per pair, g = dL/de_q (its negative is dL/de_b)
-// and adds the loss.
+// per block; pass 1 adds the counts, writes, per pair, g = dL/de_q (its
+// negative is dL/de_b) and adds the loss.
+//
+// A thread walks its hit's row, a chain of loads: one-wave workgroups spread
+// an event's hits over the chip.
+constexpr int kHingeThreads = 64;
+
+__device__ inline float wave_sum(float v) {
+#pragma unroll
+  for (int s = 32; s > 0; s >>= 1) v += __shfl_xor(v, s);
+  return v;
+}
+
 template <int D>
-__global__ __launch_bounds__(256) void k_hinge(HingeArgs A, int pass) {
+__global__ __launch_bounds__(kHingeThreads) void k_hinge(HingeArgs A, int pass) {
   if (A.status[0] != 0) return;
-  __shared__ float part[3][256];
   float n_gen = 0.f, n_fake = 0.f, loss = 0.f;
   float inv_g = 0.f, inv_f = 0.f;
   if (pass == 1) {
-    inv_g = A.counts[0] > 0.f ? 1.0f / A.counts[0] : 0.f;
-    inv_f = A.counts[1] > 0.f ? 1.0f / A.counts[1] : 0.f;
+    // the counts are whole numbers below 2^24: any order of addition gives them exactly
+    float cg = 0.f, cf = 0.f;
+    for (int i = threadIdx.x; i < (int)gridDim.x; i += kHingeThreads) {
+      cg += A.count_part[2 * i];
+      cf += A.count_part[2 * i + 1];
+    }
+    cg = wave_sum(cg);
+    cf = wave_sum(cf);
+    inv_g = cg > 0.f ? 1.0f / cg : 0.f;
+    inv_f = cf > 0.f ? 1.0f / cf : 0.f;
   }
-  for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < A.n; q += (int64_t)gridDim.x * blockDim.x) {
+  for (int64_t q = (int64_t)blockIdx.x * kHingeThreads + threadIdx.x; q < A.n; q += (int64_t)gridDim.x * kHingeThreads) {
     float eq[D], gq[D];
 #pragma unroll
     for (int k = 0; k < D; ++k) {
@@ -399,27 +371,16 @@ __global__ __launch_bounds__(256) void k_hinge(HingeArgs A, int pass) {
       for (int k = 0; k < D; ++k) A.de[q * A.ldde + k] = gq[k];
     }
   }
-  part[0][threadIdx.x] = n_gen;
-  part[1][threadIdx.x] = n_fake;
-  part[2][threadIdx.x] = loss;
-  __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s)
-      for (int j = 0; j < 3; ++j) part[j][threadIdx.x] += part[j][threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0)
-    for (int j = 0; j < 3; ++j) A.block_part[(int64_t)blockIdx.x * 3 + j] = part[j][0];
-}
-
-__global__ void k_hinge_counts(const float* __restrict__ block_part, int n_blocks, float* __restrict__ counts,
-                               float* loss_out, const int64_t* status) {
-  if (status[0] != 0) return;
-  if (blockIdx.x == 0 && threadIdx.x < 3) {
-    float s = 0.f;
-    for (int i = 0; i < n_blocks; ++i) s += block_part[(int64_t)i * 3 + threadIdx.x];
-    if (threadIdx.x < 2) counts[threadIdx.x] = s;
-    else if (loss_out) *loss_out = s;
+  if (pass == 0) {
+    n_gen = wave_sum(n_gen);
+    n_fake = wave_sum(n_fake);
+    if (threadIdx.x == 0) {
+      A.count_part[2 * blockIdx.x] = n_gen;
+      A.count_part[2 * blockIdx.x + 1] = n_fake;
+    }
+  } else {
+    loss = wave_sum(loss);
+    if (threadIdx.x == 0) A.loss_part[blockIdx.x] = loss;
   }
 }
 
@@ -427,7 +388,7 @@ __global__ void k_hinge_counts(const float* __restrict__ block_part, int n_block
 // training graph (CSC order), its predecessor's genuine pair and the random
 // pairs that picked b (given grouped by target, in order)
 template <int D>
-__global__ void k_hinge_bside(HingeArgs A) {
+__global__ __launch_bounds__(kHingeThreads) void k_hinge_bside(HingeArgs A) {
   if (A.status[0] != 0) return;
   for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < A.n; b += (int64_t)gridDim.x * blockDim.x) {
     float s[D];
@@ -452,130 +413,53 @@ __global__ void k_hinge_bside(HingeArgs A) {
   }
 }
 
-unsigned row_grid(int64_t rows, const etx_ctx* c) {
-  return (unsigned)std::max<int64_t>(1, std::min<int64_t>((rows + kRowThreads - 1) / kRowThreads, (int64_t)c->n_cu * 8));
-}
-
-unsigned flat_grid(int64_t n, const etx_ctx* c) {
-  return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, (int64_t)c->n_cu * 16));
-}
-
 }  // namespace
 
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
 
-#define BY_M(M_, FN) \
-  case M_: FN(M_); break;
-
-hipError_t launch_blk_fwd(const BlkFwd& A, int M, int act, hipStream_t s, const etx_ctx* c) {
-  if (A.rows == 0) return hipSuccess;
-  const size_t lds = sizeof(float) * ((size_t)A.K * M + M);
-  const unsigned g = row_grid(A.rows, c);
-#define L(M_)                                                                                        \
-  if (act == 2) hipLaunchKernelGGL((k_blk_fwd<M_, 2>), dim3(g), dim3(kRowThreads), lds, s, A);       \
-  else if (act == 1) hipLaunchKernelGGL((k_blk_fwd<M_, 1>), dim3(g), dim3(kRowThreads), lds, s, A); \
-  else hipLaunchKernelGGL((k_blk_fwd<M_, 0>), dim3(g), dim3(kRowThreads), lds, s, A);
-  switch (M) {
-    BY_M(1, L) BY_M(4, L) BY_M(8, L) BY_M(12, L) BY_M(16, L) BY_M(32, L) BY_M(64, L) BY_M(128, L)
+hipError_t launch_emb_fwd(const EmbTrain& A, int W, int L, const etx_ctx* c, hipStream_t s) {
+  if (A.n == 0) return hipSuccess;
+  const dim3 grid((unsigned)std::min<int64_t>((A.n + kEmbRows - 1) / kEmbRows, (int64_t)c->n_cu * 8));
+  const size_t lds = sizeof(float) * ((size_t)W * W + 2 * kEmbRows * (W + 4));
+  switch (W) {
+    case 32: hipLaunchKernelGGL(k_emb_fwd<32>, grid, dim3(kThreads), lds, s, A, L); break;
+    case 64: hipLaunchKernelGGL(k_emb_fwd<64>, grid, dim3(kThreads), lds, s, A, L); break;
+    case 128: hipLaunchKernelGGL(k_emb_fwd<128>, grid, dim3(kThreads), lds, s, A, L); break;
     default: return hipErrorInvalidValue;
   }
-#undef L
   return hipGetLastError();
 }
 
-hipError_t launch_blk_bwd(const BlkBwd& A, int M, int act, hipStream_t s, const etx_ctx* c) {
-  if (A.rows == 0) return hipSuccess;
-  const size_t lds = sizeof(float) * (size_t)A.K * M;
-  const unsigned g = row_grid(A.rows, c);
-#define L(M_)                                                                                        \
-  if (act == 2) hipLaunchKernelGGL((k_blk_bwd<M_, 2>), dim3(g), dim3(kRowThreads), lds, s, A);       \
-  else if (act == 1) hipLaunchKernelGGL((k_blk_bwd<M_, 1>), dim3(g), dim3(kRowThreads), lds, s, A); \
-  else hipLaunchKernelGGL((k_blk_bwd<M_, 0>), dim3(g), dim3(kRowThreads), lds, s, A);
-  switch (M) {
-    BY_M(1, L) BY_M(4, L) BY_M(8, L) BY_M(12, L) BY_M(16, L) BY_M(32, L) BY_M(64, L) BY_M(128, L)
+#define EMB_BWD(X)                                                                        \
+  X(32, 1) X(32, 2) X(32, 3) X(32, 4) X(64, 1) X(64, 2) X(64, 3) X(64, 4) X(128, 1)       \
+  X(128, 2) X(128, 3) X(128, 4)
+
+hipError_t launch_emb_bwd(const EmbTrain& A, int W, int L, hipStream_t s) {
+  if (A.n == 0) return hipSuccess;
+  const dim3 grid((unsigned)net_groups(A.n));
+  const size_t lds = sizeof(float) * ((size_t)W * (W + 4) + (size_t)kRows * (W + 16) + 3 * kRows);
+  switch (W * 8 + L) {
+#define X(W_, L_) \
+  case W_ * 8 + L_: hipLaunchKernelGGL((k_emb_bwd<W_, L_>), grid, dim3(kThreads), lds, s, A); break;
+    EMB_BWD(X)
+#undef X
     default: return hipErrorInvalidValue;
   }
-#undef L
   return hipGetLastError();
 }
 
-hipError_t launch_wgrad(const Wgrad& A, int M, float* grad, hipStream_t s) {
-  const int n_out = A.K * M + M;
-  const int chunks = kTrainChunks;
-  dim3 grid(chunks, (n_out + kWgradThreads - 1) / kWgradThreads);
-#define L(M_) hipLaunchKernelGGL((k_wgrad<M_>), grid, dim3(kWgradThreads), 0, s, A);
-  switch (M) {
-    BY_M(1, L) BY_M(4, L) BY_M(8, L) BY_M(12, L) BY_M(16, L) BY_M(32, L) BY_M(64, L) BY_M(128, L)
-    default: return hipErrorInvalidValue;
-  }
-#undef L
-  hipLaunchKernelGGL(k_reduce_partials, dim3((n_out + 255) / 256), dim3(256), 0, s, A.partial, chunks, n_out, grad,
-                     A.status);
-  return hipGetLastError();
-}
-#undef BY_M
-
-hipError_t launch_node_sum(int64_t n, int H, const int64_t* row_ptr, const float* a, const int64_t* col_ptr,
-                           const int32_t* csc, const float* b, float* out, int add, const int64_t* status,
-                           hipStream_t s, const etx_ctx* c) {
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_node_sum, dim3(flat_grid(n * H, c)), dim3(256), 0, s, n, H, row_ptr, a, col_ptr, csc, b, out,
-                     add, status);
-  return hipGetLastError();
+int hinge_blocks(int64_t n) {
+  return (int)std::max<int64_t>(1, std::min<int64_t>((n + kHingeThreads - 1) / kHingeThreads, kHingeBlocks));
 }
 
-hipError_t launch_edge_gather_add(int64_t E, int H, const int32_t* src, const int32_t* dst, const float* A,
-                                  const float* B, float* out, const int64_t* status, hipStream_t s, const etx_ctx* c) {
-  if (E == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_edge_gather_add, dim3(flat_grid(E * H, c)), dim3(256), 0, s, E, H, src, dst, A, B, out, status);
-  return hipGetLastError();
-}
-
-hipError_t launch_inputs(int64_t n, const float* x, const float* y, const float* z, float inv_r, float inv_z,
-                         float* cart, float* cyl, const int64_t* status, hipStream_t s, const etx_ctx* c) {
-  if (n == 0) return hipSuccess;
-  if (cart) hipLaunchKernelGGL(k_cart, dim3(flat_grid(n, c)), dim3(256), 0, s, n, x, y, z, inv_r, inv_z, cart, status);
-  if (cyl) hipLaunchKernelGGL(k_cyl, dim3(flat_grid(n, c)), dim3(256), 0, s, n, x, y, z, inv_r, inv_z, cyl, status);
-  return hipGetLastError();
-}
-
-hipError_t launch_edge_labels(int64_t E, const int32_t* src, const int32_t* dst, const int32_t* succ,
-                              const int32_t* succ2, uint8_t* lab, const int64_t* status, hipStream_t s,
-                              const etx_ctx* c) {
-  if (E == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_edge_labels, dim3(flat_grid(E, c)), dim3(256), 0, s, E, src, dst, succ, succ2, lab, status);
-  return hipGetLastError();
-}
-
-hipError_t launch_focal(int64_t E, int H, const float* cls_out, const float* w2, const uint8_t* lab, float alpha,
-                        float gamma, float* dlogit, float* dc, float* loss_part, float* loss_out, int slot,
-                        const int64_t* status, hipStream_t s, float* score) {
-  hipLaunchKernelGGL(k_focal, dim3(kTrainLossBlocks), dim3(256), 0, s, E, H, cls_out, w2, lab, alpha, gamma, dlogit,
-                     dc, loss_part, score, status);
-  hipLaunchKernelGGL(k_sum, dim3(1), dim3(64), 0, s, loss_part, kTrainLossBlocks, loss_out, slot, status);
-  return hipGetLastError();
-}
-
-hipError_t launch_adam(int64_t n, float* p, float* m, float* v, const float* g, float lr, int64_t step,
-                       const int64_t* status, hipStream_t s, const etx_ctx* c) {
-  const double b1 = 0.9, b2 = 0.999;
-  const float c1 = (float)(1.0 - std::pow(b1, (double)step)), c2 = (float)(1.0 - std::pow(b2, (double)step));
-  hipLaunchKernelGGL(k_adam, dim3(flat_grid(n, c)), dim3(256), 0, s, n, p, m, v, g, lr, (float)b1, (float)b2, 1e-8f,
-                     c1, c2, status);
-  return hipGetLastError();
-}
-
-hipError_t launch_hinge(const HingeArgs& A, int D, float* loss_out, hipStream_t s) {
-#define L(D_)                                                                                   \
-  hipLaunchKernelGGL((k_hinge<D_>), dim3(kTrainLossBlocks), dim3(256), 0, s, A, 0);             \
-  hipLaunchKernelGGL(k_hinge_counts, dim3(1), dim3(64), 0, s, A.block_part, kTrainLossBlocks,   \
-                     const_cast<float*>(A.counts), nullptr, A.status);                           \
-  hipLaunchKernelGGL((k_hinge<D_>), dim3(kTrainLossBlocks), dim3(256), 0, s, A, 1);             \
-  hipLaunchKernelGGL(k_hinge_counts, dim3(1), dim3(64), 0, s, A.block_part, kTrainLossBlocks,   \
-                     A.counts_scratch, loss_out, A.status);                                      \
-  hipLaunchKernelGGL((k_hinge_bside<D_>), dim3(256), dim3(256), 0, s, A);
+hipError_t launch_hinge(const HingeArgs& A, int D, hipStream_t s) {
+  const dim3 grid((unsigned)hinge_blocks(A.n)), block(kHingeThreads);
+#define L(D_)                                                    \
+  hipLaunchKernelGGL((k_hinge<D_>), grid, block, 0, s, A, 0);    \
+  hipLaunchKernelGGL((k_hinge<D_>), grid, block, 0, s, A, 1);    \
+  hipLaunchKernelGGL((k_hinge_bside<D_>), dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>((A.n + 63) / 64, 4096))), block, 0, s, A);
   switch (D) {
     case 4: L(4); break;
     case 8: L(8); break;
@@ -588,17 +472,14 @@ hipError_t launch_hinge(const HingeArgs& A, int D, float* loss_out, hipStream_t 
 }
 
 int train_attributes(size_t max_lds) {
-  int bad = 0;
+  int bad = train_net_attributes(max_lds);
   auto set = [&](const void* f) {
     bad |= hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_lds) != hipSuccess;
   };
-  // the widest layers (embedding hidden size 128) stage 66 KB of weights
-  set(reinterpret_cast<const void*>(k_blk_fwd<128, 0>));
-  set(reinterpret_cast<const void*>(k_blk_fwd<128, 1>));
-  set(reinterpret_cast<const void*>(k_blk_fwd<128, 2>));
-  set(reinterpret_cast<const void*>(k_blk_bwd<128, 0>));
-  set(reinterpret_cast<const void*>(k_blk_bwd<128, 1>));
-  set(reinterpret_cast<const void*>(k_blk_bwd<128, 2>));
+  set(reinterpret_cast<const void*>(k_emb_fwd<128>));
+#define X(W_, L_) set(reinterpret_cast<const void*>(k_emb_bwd<W_, L_>));
+  EMB_BWD(X)
+#undef X
   return bad;
 }
 

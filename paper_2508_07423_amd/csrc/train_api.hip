@@ -27,10 +27,9 @@ size_t a256(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct TrainLayout {
   // embedding
-  size_t cyl, emb_a[8], emb_yh[8], de, edz, edx[2], g_gen, g_rnd, g_edge, counts, counts2, hparts;
+  size_t emb_z[4], de, g_gen, g_rnd, g_edge, counts;
   // network
-  size_t cart, y1n, hst, mo, mi, t1n, yh_n, rs_n, t1ee, est, t1e, cls, yh_e, rs_e, lab, dlogit, de_e, dz_e, da_e,
-      dxs, dxd, dh, dz_n, da_n, dmo, dmi;
+  size_t hst, mo, mi, yh_n, rs_n, est, yh_e, rs_e, lab, de_e, dxs, dxd, dh, dmo, dmi;
   // shared
   size_t part, grad, lpart, loss;
   size_t total;
@@ -47,51 +46,32 @@ TrainLayout train_layout(const etx_ctx* ctx, const WsLayout& L, int64_t n, int64
     return at;
   };
   const size_t f = sizeof(float);
-  T.cyl = take(f * n * 3);
-  for (int l = 0; l < c.emb_layers + 1 && l < 8; ++l) {
-    const int64_t M = l < c.emb_layers ? W : D;
-    T.emb_a[l] = take(f * n * M);
-    T.emb_yh[l] = take(f * n * M);
-  }
+  for (int l = 0; l < c.emb_layers; ++l) T.emb_z[l] = take(f * n * W);
   T.de = take(f * n * kDpad);
-  T.edz = take(f * n * std::max<int64_t>(W, H));
-  T.edx[0] = take(f * n * std::max<int64_t>(W, 3 * H));
-  T.edx[1] = take(f * n * std::max<int64_t>(W, 3 * H));
   T.g_gen = take(f * n * D);
   T.g_rnd = take(f * n * D);
   T.g_edge = take(f * E * D);
-  T.counts = take(f * 2);
-  T.counts2 = take(f * 2);
-  T.hparts = take(f * 3 * kTrainLossBlocks);
-  T.cart = take(f * n * 3);
-  T.y1n = take(f * n * H);
+  T.counts = take(f * 2 * kHingeBlocks);
   T.hst = take(f * (S + 1) * n * H);
   T.mo = take(f * S * n * H);
   T.mi = take(f * S * n * H);
-  T.t1n = take(f * S * n * H);
   T.yh_n = take(f * (2 + 2 * S) * n * H);
   T.rs_n = take(f * (2 + 2 * S) * n);
-  T.t1ee = take(f * E * H);
   T.est = take(f * (S + 1) * E * H);
-  T.t1e = take(f * S * E * H);
-  T.cls = take(f * E * H);
-  T.yh_e = take(f * (3 + 2 * S) * E * H);
-  T.rs_e = take(f * (3 + 2 * S) * E);
+  T.yh_e = take(f * (2 + 2 * S) * E * H);
+  T.rs_e = take(f * (2 + 2 * S) * E);
   T.lab = take(E);
-  T.dlogit = take(f * E);
   T.de_e = take(f * E * H);
-  T.dz_e = take(f * E * H);
-  T.da_e = take(f * E * H);
   T.dxs = take(f * E * H);
   T.dxd = take(f * E * H);
   T.dh = take(f * n * H);
-  T.dz_n = take(f * n * std::max<int64_t>(H, W));
-  T.da_n = take(f * n * H);
   T.dmo = take(f * n * H);
   T.dmi = take(f * n * H);
-  T.part = take(f * kTrainChunks * (std::max<int64_t>(3 * H, W) * std::max<int64_t>(H, W) + std::max<int64_t>(H, W)));
-  T.grad = take(f * blob_floats_of(c));
-  T.lpart = take(f * kTrainLossBlocks);
+  // gradient partials: the embedding's over hits, the network's over hits and edges
+  const size_t P = blob_floats_of(c);
+  T.part = take(f * P * kTrainChunks);
+  T.grad = take(f * P);
+  T.lpart = take(f * std::max(3 * kTrainChunks, kHingeBlocks));
   T.loss = take(f * 4);
   T.total = o;
   return T;
@@ -99,8 +79,7 @@ TrainLayout train_layout(const etx_ctx* ctx, const WsLayout& L, int64_t n, int64
 
 // The triplet part of a network step's workspace (after the TrainLayout).
 struct TripLayout {
-  size_t ta, tb, kind, tscore, art_off, elb_off, tstatus, tri, lab, yh1, y1, rs1, yh2, y2, rs2, dlogit, dc, dz, da,
-      dxa, dxb, tgrad, total;
+  size_t ta, tb, kind, tscore, art_off, elb_off, tstatus, tri, lab, dxa, dxb, part, tgrad, total;
   TriLayout TL;
 };
 
@@ -124,18 +103,9 @@ TripLayout trip_layout(const etx_ctx* ctx, size_t base, int64_t n_events, int64_
   X.TL = tri_layout(n_events, n, E, tcap, 0);
   X.tri = take(X.TL.total);
   X.lab = take(T);
-  X.yh1 = take(f * T * H);
-  X.y1 = take(f * T * H);
-  X.rs1 = take(f * T);
-  X.yh2 = take(f * T * H);
-  X.y2 = take(f * T * H);
-  X.rs2 = take(f * T);
-  X.dlogit = take(f * T);
-  X.dc = take(f * T * H);
-  X.dz = take(f * T * H);
-  X.da = take(f * T * H);
   X.dxa = take(f * T * H);
   X.dxb = take(f * T * H);
+  X.part = take(f * ETX_TRIPLET_NPARAM(H) * kTrainChunks);
   X.tgrad = take(f * ETX_TRIPLET_NPARAM(H));
   X.total = o;
   return X;
@@ -177,9 +147,6 @@ ParamMap param_map(const etx_config& c) {
   P.total = o;
   return P;
 }
-
-TrainSeg seg(const float* base, const int32_t* idx, int width, int ld) { return TrainSeg{base, idx, width, ld}; }
-TrainOut tout(float* base, int width, int ld, int add) { return TrainOut{base, width, ld, add}; }
 
 }  // namespace
 }  // namespace etx
@@ -383,27 +350,29 @@ etx_status etx_train_embed_step(etx_ctx* ctx, const etx_hits* hits, etx_out* out
   float* prm = ctx->dev_train;
   float* grad = F(T.grad);
   const int64_t* status = out->status;
-  const int W = c.emb_hidden, D = c.emb_dim, NL = c.emb_layers + 1;
+  const int W = c.emb_hidden, D = c.emb_dim;
   HIPCHK(build_graph(a, false));
-  // training embedding: forward, keeping every layer's z and output; the output goes to the embedding buffer
-  HIPCHK(launch_inputs(n, hits->x, hits->y, hits->z, 1.0f / c.r_scale_mm, 1.0f / c.z_scale_mm, nullptr, F(T.cyl),
-                       status, s, ctx));
-  for (int l = 0; l < NL; ++l) {
-    const int K = l == 0 ? 3 : W, M = l + 1 < NL ? W : D;
-    BlkFwd A{};
-    A.rows = n;
-    A.seg[0] = seg(l == 0 ? F(T.cyl) : F(T.emb_a[l - 1]), nullptr, K, K);
-    A.nseg = 1;
-    A.K = K;
-    A.W = prm + P.emb[l];
-    A.yhat = F(T.emb_yh[l]);
-    const bool last = l + 1 == NL;
-    A.y = last ? F(L.emb) : F(T.emb_a[l]);
-    A.ldy = last ? kDpad : M;
-    A.pad_zero = last ? 1 : 0;
-    A.status = status;
-    HIPCHK(launch_blk_fwd(A, M, last ? 0 : 1, s, ctx));
+  // training embedding: forward, keeping every hidden layer's z; the output goes to the embedding buffer
+  const int NL = c.emb_layers;
+  EmbTrain Em{};
+  Em.n = n;
+  Em.x = hits->x;
+  Em.y = hits->y;
+  Em.z = hits->z;
+  Em.inv_r = 1.0f / c.r_scale_mm;
+  Em.inv_z = 1.0f / c.z_scale_mm;
+  for (int l = 0; l <= NL; ++l) {
+    Em.W[l] = prm + P.emb[l];
+    Em.o[l] = P.emb[l];
+    if (l < NL) Em.zs[l] = F(T.emb_z[l]);
   }
+  Em.emb = F(L.emb);
+  Em.de = F(T.de);
+  Em.D = D;
+  Em.part = F(T.part);
+  Em.part_stride = P.gnn_begin;
+  Em.status = status;
+  HIPCHK(launch_emb_fwd(Em, W, NL, ctx, s));
   // hard negatives: the radius graph of the training embedding at the training radius
   RunArgs ar = a;
   ar.radius_override = r_train;
@@ -425,45 +394,33 @@ etx_status etx_train_embed_step(etx_ctx* ctx, const etx_hits* hits, etx_out* out
   Hg.csc = reinterpret_cast<const int32_t*>(ws + L.csc);
   Hg.margin = margin;
   Hg.w_gen = w_gen;
-  Hg.counts = F(T.counts);
-  Hg.counts_scratch = F(T.counts2);
-  Hg.block_part = F(T.hparts);
+  Hg.count_part = F(T.counts);
+  Hg.loss_part = F(T.lpart);
   Hg.g_gen = F(T.g_gen);
   Hg.g_rnd = F(T.g_rnd);
   Hg.g_edge = F(T.g_edge);
   Hg.de = F(T.de);
   Hg.ldde = kDpad;
   Hg.status = status;
-  HIPCHK(launch_hinge(Hg, D, F(T.loss), s));
-  // backward through the layers
-  for (int l = NL - 1; l >= 0; --l) {
-    const int K = l == 0 ? 3 : W, M = l + 1 < NL ? W : D;
-    BlkBwd B{};
-    B.rows = n;
-    B.dy = l + 1 == NL ? F(T.de) : F(T.edx[l % 2]);
-    B.lddy = l + 1 == NL ? kDpad : M;
-    B.yhat = F(T.emb_yh[l]);
-    B.W = prm + P.emb[l];
-    B.K = K;
-    B.dz = F(T.edz);
-    B.out[0] = tout(l > 0 ? F(T.edx[(l + 1) % 2]) : nullptr, K, K, 0);
-    B.nseg = 1;
-    B.status = status;
-    HIPCHK(launch_blk_bwd(B, M, l + 1 == NL ? 0 : 1, s, ctx));
-    Wgrad G{};
-    G.rows = n;
-    G.seg[0] = seg(l == 0 ? F(T.cyl) : F(T.emb_a[l - 1]), nullptr, K, K);
-    G.nseg = 1;
-    G.K = K;
-    G.dz = F(T.edz);
-    G.partial = F(T.part);
-    G.status = status;
-    HIPCHK(launch_wgrad(G, M, grad + P.emb[l], s));
-  }
-  const int64_t np = P.gnn_begin;
+  HIPCHK(launch_hinge(Hg, D, s));
+  HIPCHK(launch_emb_bwd(Em, W, NL, s));
   const int64_t nb = (int64_t)blob_floats_of(c);
-  if (lr > 0) HIPCHK(launch_adam(np, prm, prm + nb, prm + 2 * nb, grad, lr, step, status, s, ctx));
-  if (loss_dev) HIPCHK(hipMemcpyAsync(loss_dev, F(T.loss), sizeof(float), hipMemcpyDeviceToDevice, s));
+  GradAdam G{};
+  G.set[0].part = F(T.part);
+  G.set[0].stride = P.gnn_begin;
+  G.set[0].n = G.set[0].b0 = P.gnn_begin;
+  G.set[0].g0 = net_groups(n);
+  G.set[0].grad = grad;
+  G.set[0].p = prm;
+  G.set[0].m = prm + nb;
+  G.set[0].v = prm + 2 * nb;
+  G.lr = lr;
+  G.loss_part[0] = F(T.lpart);
+  G.loss_n[0] = hinge_blocks(n);
+  G.loss = F(T.loss);
+  G.loss_dev = loss_dev;
+  G.status = status;
+  HIPCHK(launch_grad_adam(G, step, s));
   return ETX_OK;
 }
 
@@ -512,100 +469,82 @@ etx_status gnn_step(etx_ctx* ctx, const etx_hits* hits, etx_out* out, const etx_
   HIPCHK(hipMemcpyAsync(dev_status, out->status, sizeof(dev_status), hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
   if (dev_status[0] != ETX_OK) return static_cast<etx_status>(dev_status[0]);
-  const int32_t* src = out->src;
-  const int32_t* dst = out->dst;
-  const int64_t* row_ptr = reinterpret_cast<const int64_t*>(ws + L.row_ptr);
-  const int64_t* col_ptr = reinterpret_cast<const int64_t*>(ws + L.col_ptr);
-  const int32_t* csc = reinterpret_cast<const int32_t*>(ws + L.csc);
   const int64_t nH = n * H, eH = E * H;
   auto hst = [&](int k) { return F(T.hst) + k * nH; };
   auto est = [&](int k) { return F(T.est) + k * eH; };
-  auto yhn = [&](int j) { return F(T.yh_n) + j * nH; };
-  auto rsn = [&](int j) { return F(T.rs_n) + j * n; };
-  auto yhe = [&](int j) { return F(T.yh_e) + j * eH; };
-  auto rse = [&](int j) { return F(T.rs_e) + j * E; };
-  // node-row block j: 0 ne1, 1 ne2, 2 + 2k nn1_k, 3 + 2k nn2_k; edge-row block j: 0 ee1, 1 ee2, 2 + 2k en1_k,
-  // 3 + 2k en2_k, 2 + 2S cls
-  auto fwd = [&](int64_t rows, std::initializer_list<TrainSeg> segs, const float* Wp, float* yh, float* rs, float* y,
-                 const float* resid) {
-    BlkFwd A{};
-    A.rows = rows;
-    int i = 0, K = 0;
-    for (const TrainSeg& g : segs) {
-      A.seg[i++] = g;
-      K += g.width;
-    }
-    A.nseg = i;
-    A.K = K;
-    A.W = Wp;
-    A.yhat = yh;
-    A.rstd = rs;
-    A.y = y;
-    A.ldy = H;
-    A.resid = resid;
-    A.status = status;
-    return launch_blk_fwd(A, H, 2, s, ctx);
+  // layers j of node rows: 0 ne1, 1 ne2, 2 + 2k nn1_k, 3 + 2k nn2_k; of edge rows: 0 ee1, 1 ee2, 2 + 2k en1_k, 3 + 2k en2_k
+  NetStep base{};
+  base.n = n;
+  base.E = E;
+  base.x = hits->x;
+  base.y = hits->y;
+  base.z = hits->z;
+  base.inv_r = 1.0f / c.r_scale_mm;
+  base.inv_z = 1.0f / c.z_scale_mm;
+  base.row_ptr = reinterpret_cast<const int64_t*>(ws + L.row_ptr);
+  base.col_ptr = reinterpret_cast<const int64_t*>(ws + L.col_ptr);
+  base.csc = reinterpret_cast<const int32_t*>(ws + L.csc);
+  base.src = out->src;
+  base.dst = out->dst;
+  base.lab = reinterpret_cast<uint8_t*>(ws + T.lab);
+  base.succ = truth->succ;
+  base.succ2 = truth->succ2;
+  base.alpha = alpha;
+  base.gamma = gamma;
+  base.lpart = F(T.lpart);
+  base.score = trip ? out->score : nullptr;
+  base.de = F(T.de_e);
+  base.dxs = F(T.dxs);
+  base.dxd = F(T.dxd);
+  base.dh = F(T.dh);
+  base.dmo = F(T.dmo);
+  base.dmi = F(T.dmi);
+  base.part = F(T.part);
+  const int64_t g0 = P.gnn_begin, ng = P.total - P.gnn_begin;
+  base.part_stride = ng;
+  base.Wc = prm + P.cls1;
+  base.Wl = prm + P.cls2;
+  base.oc = P.cls1 - g0;
+  base.ol = P.cls2 - g0;
+  auto stage = [&](bool edges, int j, int64_t p1, int64_t p2) {
+    NetStep A = base;
+    A.W1 = prm + p1;
+    A.W2 = prm + p2;
+    A.o1 = p1 - g0;
+    A.o2 = p2 - g0;
+    A.yh1 = edges ? F(T.yh_e) + j * eH : F(T.yh_n) + j * nH;
+    A.yh2 = edges ? F(T.yh_e) + (j + 1) * eH : F(T.yh_n) + (j + 1) * nH;
+    A.rs1 = edges ? F(T.rs_e) + j * E : F(T.rs_n) + j * n;
+    A.rs2 = edges ? F(T.rs_e) + (j + 1) * E : F(T.rs_n) + (j + 1) * n;
+    return A;
   };
-  auto bwd = [&](int64_t rows, const float* dy, const float* dy2, const float* yh, const float* rs, const float* Wp,
-                 int K, float* dz, std::initializer_list<TrainOut> outs) {
-    BlkBwd B{};
-    B.rows = rows;
-    B.dy = dy;
-    B.dy2 = dy2;
-    B.lddy = H;
-    B.yhat = yh;
-    B.rstd = rs;
-    B.W = Wp;
-    B.K = K;
-    B.dz = dz;
-    int i = 0;
-    for (const TrainOut& o : outs) B.out[i++] = o;
-    B.nseg = i;
-    B.status = status;
-    return launch_blk_bwd(B, H, 2, s, ctx);
+  auto node_stage = [&](int k) {
+    NetStep A = stage(false, 2 + 2 * k, P.nn1[k], P.nn2[k]);
+    A.mo = F(T.mo) + k * nH;
+    A.mi = F(T.mi) + k * nH;
+    A.h_in = hst(k);
+    A.h_out = hst(k + 1);
+    A.e_in = est(k);
+    return A;
   };
-  auto wg = [&](int64_t rows, std::initializer_list<TrainSeg> segs, const float* dz, int M, int64_t goff) {
-    Wgrad G{};
-    G.rows = rows;
-    int i = 0, K = 0;
-    for (const TrainSeg& g : segs) {
-      G.seg[i++] = g;
-      K += g.width;
-    }
-    G.nseg = i;
-    G.K = K;
-    G.dz = dz;
-    G.partial = F(T.part);
-    G.status = status;
-    return launch_wgrad(G, M, grad + goff, s);
+  auto edge_stage = [&](int k) {
+    NetStep A = stage(true, 2 + 2 * k, P.en1[k], P.en2[k]);
+    A.e_in = est(k);
+    A.e_out = est(k + 1);
+    A.h_in = hst(k + 1);
+    return A;
   };
-  // ---- forward
-  HIPCHK(launch_edge_labels(E, src, dst, truth->succ, truth->succ2, reinterpret_cast<uint8_t*>(ws + T.lab), status, s,
-                            ctx));
-  HIPCHK(launch_inputs(n, hits->x, hits->y, hits->z, 1.0f / c.r_scale_mm, 1.0f / c.z_scale_mm, F(T.cart), nullptr,
-                       status, s, ctx));
-  HIPCHK(fwd(n, {seg(F(T.cart), nullptr, 3, 3)}, prm + P.ne1, yhn(0), rsn(0), F(T.y1n), nullptr));
-  HIPCHK(fwd(n, {seg(F(T.y1n), nullptr, H, H)}, prm + P.ne2, yhn(1), rsn(1), hst(0), nullptr));
-  HIPCHK(fwd(E, {seg(hst(0), src, H, H), seg(hst(0), dst, H, H)}, prm + P.ee1, yhe(0), rse(0), F(T.t1ee), nullptr));
-  HIPCHK(fwd(E, {seg(F(T.t1ee), nullptr, H, H)}, prm + P.ee2, yhe(1), rse(1), est(0), nullptr));
+  NetStep node_enc = stage(false, 0, P.ne1, P.ne2), edge_enc = stage(true, 0, P.ee1, P.ee2);
+  node_enc.h_out = hst(0);
+  edge_enc.h_in = hst(0);
+  edge_enc.e_out = est(0);
+  // ---- forward; the last edge update also runs the classifier, forward and backward
+  HIPCHK(launch_net(NET_NODE_ENC, node_enc, H, s));
+  HIPCHK(launch_net(NET_EDGE_ENC, edge_enc, H, s));
   for (int k = 0; k < S; ++k) {
-    float* mo = F(T.mo) + k * nH;
-    float* mi = F(T.mi) + k * nH;
-    HIPCHK(launch_node_sum(n, H, row_ptr, est(k), col_ptr, csc, nullptr, mo, 0, status, s, ctx));
-    HIPCHK(launch_node_sum(n, H, row_ptr, nullptr, col_ptr, csc, est(k), mi, 0, status, s, ctx));
-    float* t1n = F(T.t1n) + k * nH;
-    HIPCHK(fwd(n, {seg(hst(k), nullptr, H, H), seg(mo, nullptr, H, H), seg(mi, nullptr, H, H)}, prm + P.nn1[k],
-               yhn(2 + 2 * k), rsn(2 + 2 * k), t1n, nullptr));
-    HIPCHK(fwd(n, {seg(t1n, nullptr, H, H)}, prm + P.nn2[k], yhn(3 + 2 * k), rsn(3 + 2 * k), hst(k + 1), hst(k)));
-    float* t1e = F(T.t1e) + k * eH;
-    HIPCHK(fwd(E, {seg(est(k), nullptr, H, H), seg(hst(k + 1), src, H, H), seg(hst(k + 1), dst, H, H)},
-               prm + P.en1[k], yhe(2 + 2 * k), rse(2 + 2 * k), t1e, nullptr));
-    HIPCHK(fwd(E, {seg(t1e, nullptr, H, H)}, prm + P.en2[k], yhe(3 + 2 * k), rse(3 + 2 * k), est(k + 1), est(k)));
+    HIPCHK(launch_net(NET_NODE, node_stage(k), H, s));
+    HIPCHK(launch_net(k + 1 < S ? NET_EDGE : NET_EDGE_LAST, edge_stage(k), H, s));
   }
-  const int jc = 2 + 2 * S;
-  HIPCHK(fwd(E, {seg(est(S), nullptr, H, H)}, prm + P.cls1, yhe(jc), rse(jc), F(T.cls), nullptr));
-  HIPCHK(launch_focal(E, H, F(T.cls), prm + P.cls2, reinterpret_cast<const uint8_t*>(ws + T.lab), alpha, gamma,
-                      F(T.dlogit), F(T.da_e), F(T.lpart), F(T.loss), 0, status, s, trip ? out->score : nullptr));
   // ---- triplets of the purified graph of this step's scores, and the two classifiers on them
   etx_tracks TS{};
   int64_t nrow[2] = {0, 0};
@@ -634,96 +573,73 @@ etx_status gnn_step(etx_ctx* ctx, const etx_hits* hits, etx_out* out, const etx_
     nrow[1] = cnt[1];
     uint8_t* tlab = reinterpret_cast<uint8_t*>(ws + X.lab);
     HIPCHK(launch_tri_labels(a, ws + X.tri, X.TL, TS, *truth, tlab));
-    HIPCHK(hipMemsetAsync(F(X.tgrad), 0, sizeof(float) * 2 * hsz, s));
-    HIPCHK(hipMemsetAsync(F(T.loss) + 1, 0, sizeof(float) * 2, s));
-    for (int hd = 0; hd < 2; ++hd) {
-      const int64_t nh = nrow[hd], r0 = hd ? nrow[0] : 0;
-      if (nh == 0) continue;
-      const float* hp = tprm + hd * hsz;
-      HIPCHK(fwd(nh, {seg(est(S), TS.tri_a + r0, H, H), seg(est(S), TS.tri_b + r0, H, H)}, hp, F(X.yh1) + r0 * H,
-                 F(X.rs1) + r0, F(X.y1) + r0 * H, nullptr));
-      HIPCHK(fwd(nh, {seg(F(X.y1) + r0 * H, nullptr, H, H)}, hp + 2 * H * H + H, F(X.yh2) + r0 * H, F(X.rs2) + r0,
-                 F(X.y2) + r0 * H, nullptr));
-      HIPCHK(launch_focal(nh, H, F(X.y2) + r0 * H, hp + 3 * H * H + 2 * H, tlab + r0, alpha, gamma, F(X.dlogit) + r0,
-                          F(X.dc) + r0 * H, F(T.lpart), F(T.loss), 1 + hd, status, s));
-    }
-  }
-  // ---- backward
-  HIPCHK(wg(E, {seg(F(T.cls), nullptr, H, H)}, F(T.dlogit), 1, P.cls2));
-  HIPCHK(bwd(E, F(T.da_e), nullptr, yhe(jc), rse(jc), prm + P.cls1, H, F(T.dz_e), {tout(F(T.de_e), H, H, 0)}));
-  HIPCHK(wg(E, {seg(est(S), nullptr, H, H)}, F(T.dz_e), H, P.cls1));
-  if (trip) {
-    auto wgt = [&](int64_t rows, std::initializer_list<TrainSeg> segs, const float* dz, int M, float* gp) {
-      Wgrad G{};
-      G.rows = rows;
-      int i = 0, K = 0;
-      for (const TrainSeg& g : segs) {
-        G.seg[i++] = g;
-        K += g.width;
-      }
-      G.nseg = i;
-      G.K = K;
-      G.dz = dz;
-      G.partial = F(T.part);
-      G.status = status;
-      return launch_wgrad(G, M, gp, s);
-    };
-    for (int hd = 0; hd < 2; ++hd) {
-      const int64_t nh = nrow[hd], r0 = hd ? nrow[0] : 0;
-      if (nh == 0) continue;
-      const float* hp = tprm + hd * hsz;
-      float* hg = F(X.tgrad) + hd * hsz;
-      HIPCHK(wgt(nh, {seg(F(X.y2) + r0 * H, nullptr, H, H)}, F(X.dlogit) + r0, 1, hg + 3 * H * H + 2 * H));
-      HIPCHK(bwd(nh, F(X.dc) + r0 * H, nullptr, F(X.yh2) + r0 * H, F(X.rs2) + r0, hp + 2 * H * H + H, H, F(X.dz),
-                 {tout(F(X.da), H, H, 0)}));
-      HIPCHK(wgt(nh, {seg(F(X.y1) + r0 * H, nullptr, H, H)}, F(X.dz), H, hg + 2 * H * H + H));
-      HIPCHK(bwd(nh, F(X.da), nullptr, F(X.yh1) + r0 * H, F(X.rs1) + r0, hp, 2 * H, F(X.dz),
-                 {tout(F(X.dxa) + r0 * H, H, H, 0), tout(F(X.dxb) + r0 * H, H, H, 0)}));
-      HIPCHK(wgt(nh, {seg(est(S), TS.tri_a + r0, H, H), seg(est(S), TS.tri_b + r0, H, H)}, F(X.dz), H, hg));
-    }
+    TriTrain R{};
+    R.rows[0] = nrow[0];
+    R.rows[1] = nrow[1];
+    R.prm = tprm;
+    R.e = est(S);
+    R.tri_a = TS.tri_a;
+    R.tri_b = TS.tri_b;
+    R.lab = tlab;
+    R.alpha = alpha;
+    R.gamma = gamma;
+    R.dxa = F(X.dxa);
+    R.dxb = F(X.dxb);
+    R.lpart = F(T.lpart) + kTrainChunks;
+    R.part = F(X.part);
+    R.part_stride = 2 * hsz;
+    HIPCHK(launch_tri_train(R, H, s));
     HIPCHK(launch_tri_edge_grad(a, ws + X.tri, X.TL, TS, F(X.dxa), F(X.dxb), F(T.de_e)));
   }
+  // ---- backward
   for (int k = S - 1; k >= 0; --k) {
-    float* t1e = F(T.t1e) + k * eH;
-    // edge update k
-    HIPCHK(bwd(E, F(T.de_e), nullptr, yhe(3 + 2 * k), rse(3 + 2 * k), prm + P.en2[k], H, F(T.dz_e),
-               {tout(F(T.da_e), H, H, 0)}));
-    HIPCHK(wg(E, {seg(t1e, nullptr, H, H)}, F(T.dz_e), H, P.en2[k]));
-    HIPCHK(bwd(E, F(T.da_e), nullptr, yhe(2 + 2 * k), rse(2 + 2 * k), prm + P.en1[k], 3 * H, F(T.dz_e),
-               {tout(F(T.de_e), H, H, 1), tout(F(T.dxs), H, H, 0), tout(F(T.dxd), H, H, 0)}));
-    HIPCHK(wg(E, {seg(est(k), nullptr, H, H), seg(hst(k + 1), src, H, H), seg(hst(k + 1), dst, H, H)}, F(T.dz_e),
-              H, P.en1[k]));
-    HIPCHK(launch_node_sum(n, H, row_ptr, F(T.dxs), col_ptr, csc, F(T.dxd), F(T.dh), k == S - 1 ? 0 : 1, status, s,
-                           ctx));
-    // node update k
-    float* t1n = F(T.t1n) + k * nH;
-    HIPCHK(bwd(n, F(T.dh), nullptr, yhn(3 + 2 * k), rsn(3 + 2 * k), prm + P.nn2[k], H, F(T.dz_n),
-               {tout(F(T.da_n), H, H, 0)}));
-    HIPCHK(wg(n, {seg(t1n, nullptr, H, H)}, F(T.dz_n), H, P.nn2[k]));
-    HIPCHK(bwd(n, F(T.da_n), nullptr, yhn(2 + 2 * k), rsn(2 + 2 * k), prm + P.nn1[k], 3 * H, F(T.dz_n),
-               {tout(F(T.dh), H, H, 1), tout(F(T.dmo), H, H, 0), tout(F(T.dmi), H, H, 0)}));
-    HIPCHK(wg(n, {seg(hst(k), nullptr, H, H), seg(F(T.mo) + k * nH, nullptr, H, H), seg(F(T.mi) + k * nH, nullptr, H, H)},
-              F(T.dz_n), H, P.nn1[k]));
-    HIPCHK(launch_edge_gather_add(E, H, src, dst, F(T.dmo), F(T.dmi), F(T.de_e), status, s, ctx));
+    NetStep Ae = edge_stage(k), An = node_stage(k);
+    if (k == S - 1) Ae.dmo = nullptr;
+    An.add_dh = k < S - 1;
+    HIPCHK(launch_net(NET_EDGE_BWD, Ae, H, s));
+    HIPCHK(launch_net(NET_NODE_BWD, An, H, s));
   }
-  // edge encoder, node encoder
-  HIPCHK(bwd(E, F(T.de_e), nullptr, yhe(1), rse(1), prm + P.ee2, H, F(T.dz_e), {tout(F(T.da_e), H, H, 0)}));
-  HIPCHK(wg(E, {seg(F(T.t1ee), nullptr, H, H)}, F(T.dz_e), H, P.ee2));
-  HIPCHK(bwd(E, F(T.da_e), nullptr, yhe(0), rse(0), prm + P.ee1, 2 * H, F(T.dz_e),
-             {tout(F(T.dxs), H, H, 0), tout(F(T.dxd), H, H, 0)}));
-  HIPCHK(wg(E, {seg(hst(0), src, H, H), seg(hst(0), dst, H, H)}, F(T.dz_e), H, P.ee1));
-  HIPCHK(launch_node_sum(n, H, row_ptr, F(T.dxs), col_ptr, csc, F(T.dxd), F(T.dh), S > 0 ? 1 : 0, status, s, ctx));
-  HIPCHK(bwd(n, F(T.dh), nullptr, yhn(1), rsn(1), prm + P.ne2, H, F(T.dz_n), {tout(F(T.da_n), H, H, 0)}));
-  HIPCHK(wg(n, {seg(F(T.y1n), nullptr, H, H)}, F(T.dz_n), H, P.ne2));
-  HIPCHK(bwd(n, F(T.da_n), nullptr, yhn(0), rsn(0), prm + P.ne1, 3, F(T.dz_n), {tout(nullptr, 3, 3, 0)}));
-  HIPCHK(wg(n, {seg(F(T.cart), nullptr, 3, 3)}, F(T.dz_n), H, P.ne1));
+  node_enc.add_dh = 1;
+  HIPCHK(launch_net(NET_EDGE_ENC_BWD, edge_enc, H, s));
+  HIPCHK(launch_net(NET_NODE_ENC_BWD, node_enc, H, s));
+  // ---- gradients and Adam
   const int64_t nb = (int64_t)blob_floats_of(c);
-  const int64_t g0 = P.gnn_begin, ng = P.total - P.gnn_begin;
-  if (lr > 0) HIPCHK(launch_adam(ng, prm + g0, prm + nb + g0, prm + 2 * nb + g0, grad + g0, lr, step, status, s, ctx));
-  if (trip && lr > 0)
-    HIPCHK(launch_adam(2 * hsz, tprm, tprm + 2 * hsz, tprm + 4 * hsz, F(X.tgrad), lr, step, status, s, ctx));
-  if (loss_dev)
-    HIPCHK(hipMemcpyAsync(loss_dev, F(T.loss), sizeof(float) * (trip ? 3 : 1), hipMemcpyDeviceToDevice, s));
+  const int gn = net_groups(n), ge = net_groups(E);
+  GradAdam G{};
+  G.set[0].part = F(T.part);
+  G.set[0].stride = ng;
+  G.set[0].n = ng;
+  G.set[0].b0 = P.ee1 - g0;
+  G.set[0].b1 = P.nn1[0] - g0;
+  G.set[0].b2 = P.cls1 - g0;
+  G.set[0].half = P.en1[0] - P.nn1[0];
+  G.set[0].g0 = gn;
+  G.set[0].g1 = ge;
+  G.set[0].grad = grad + g0;
+  G.set[0].p = prm + g0;
+  G.set[0].m = prm + nb + g0;
+  G.set[0].v = prm + 2 * nb + g0;
+  G.lr = lr;
+  G.loss_part[0] = F(T.lpart);
+  G.loss_n[0] = ge;
+  if (trip) {
+    G.set[1].part = F(X.part);
+    G.set[1].stride = G.set[1].n = G.set[1].b1 = 2 * hsz;
+    G.set[1].b0 = hsz;
+    G.set[1].g0 = net_groups(nrow[0]);
+    G.set[1].g1 = net_groups(nrow[1]);
+    G.set[1].grad = F(X.tgrad);
+    G.set[1].p = tprm;
+    G.set[1].m = tprm + 2 * hsz;
+    G.set[1].v = tprm + 4 * hsz;
+    for (int hd = 0; hd < 2; ++hd) {
+      G.loss_part[1 + hd] = F(T.lpart) + (1 + hd) * kTrainChunks;
+      G.loss_n[1 + hd] = net_groups(nrow[hd]);
+    }
+  }
+  G.loss = F(T.loss);
+  G.loss_dev = loss_dev;
+  HIPCHK(launch_grad_adam(G, step, s));
   return ETX_OK;
 }
 
