@@ -80,36 +80,60 @@ __global__ void k_validate(int64_t n_events, int64_t n_hits, const int64_t* __re
 // plane bucketing: per event, a stable counting sort of hits by plane
 // --------------------------------------------------------------------------
 
+// Every thread counts a contiguous chunk of hits per plane; the waves then scan
+// the 256 counts of a plane each (four per lane) and one wave the plane totals,
+// so the block meets three times, not twice per plane, and eight plane numbers
+// of a chunk load together: a chain of loads and barriers is all the kernel's
+// time (one 1,820-hit event 14 -> 7 us).
 __global__ __launch_bounds__(256) void k_bucket(const int64_t* __restrict__ hit_off, const int32_t* __restrict__ plane,
                                                 int n_planes, int32_t* __restrict__ bucket,
                                                 int32_t* __restrict__ plane_off, const int64_t* status) {
+  constexpr int kBatch = 8;
+  extern __shared__ __align__(16) int cnt[];            // [n_planes][256]
+  __shared__ int base[ETX_MAX_PLANES];
   if (status[0] != 0) return;
-  extern __shared__ int cnt[];            // [n_planes][256]
-  __shared__ int tmp[4];
-  const int ev = blockIdx.x, t = threadIdx.x;
+  const int ev = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int64_t a = hit_off[ev];
   const int n = (int)(hit_off[ev + 1] - a);
   const int chunk = (n + 255) / 256;
   const int lo = min(n, t * chunk), hi = min(n, lo + chunk);
   for (int p = 0; p < n_planes; ++p) cnt[p * 256 + t] = 0;
-  for (int i = lo; i < hi; ++i) cnt[plane[a + i] * 256 + t] += 1;
+  auto each = [&](auto f) {
+    for (int i0 = lo; i0 < hi; i0 += kBatch) {
+      int pl[kBatch];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) pl[u] = i0 + u < hi ? plane[a + i0 + u] : -1;
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u)
+        if (pl[u] >= 0) f(i0 + u, pl[u]);
+    }
+  };
+  each([&](int, int p) { cnt[p * 256 + t] += 1; });
   __syncthreads();
-  int base = 0;
-  int32_t* po = plane_off + (int64_t)ev * (n_planes + 1);
-  for (int p = 0; p < n_planes; ++p) {
-    int total;
-    int ex = block_exclusive_scan(cnt[p * 256 + t], tmp, total);
-    cnt[p * 256 + t] = base + ex;
-    if (t == 0) po[p] = base;
-    base += total;
+  for (int p = wave; p < n_planes; p += 4) {
+    int4 v = *reinterpret_cast<int4*>(cnt + p * 256 + 4 * lane);
+    const int sum = v.x + v.y + v.z + v.w, inc = wave_inclusive_scan(sum);
+    if (lane == 63) base[p] = inc;
+    int e = inc - sum;
+    const int4 c = v;
+    v.x = e;
+    v.y = e += c.x;
+    v.z = e += c.y;
+    v.w = e + c.z;
+    *reinterpret_cast<int4*>(cnt + p * 256 + 4 * lane) = v;
   }
-  if (t == 0) po[n_planes] = n;
   __syncthreads();
-  for (int i = lo; i < hi; ++i) {
-    int p = plane[a + i];
-    int pos = cnt[p * 256 + t]++;
-    bucket[a + pos] = (int32_t)(a + i);
+  if (wave == 0) {
+    const int tot = lane < n_planes ? base[lane] : 0, ex = wave_inclusive_scan(tot) - tot;
+    int32_t* po = plane_off + (int64_t)ev * (n_planes + 1);
+    if (lane < n_planes) {
+      base[lane] = ex;
+      po[lane] = ex;
+    }
+    if (lane == 0) po[n_planes] = n;
   }
+  __syncthreads();
+  each([&](int i, int p) { bucket[a + base[p] + cnt[p * 256 + t]++] = (int32_t)(a + i); });
 }
 
 // --------------------------------------------------------------------------
@@ -135,6 +159,16 @@ __global__ __launch_bounds__(256) void k_scan_reduce(const int32_t* __restrict__
   if (threadIdx.x == 0) part[b] = red[0];
 }
 
+// Reports more edges than the caller's capacity or than 32-bit edge ids hold;
+// returns the status code.
+__device__ inline int64_t check_edges(int64_t edges, int64_t capacity, int64_t* status) {
+  if (edges <= capacity && edges < 0x7fffffffLL) return ETX_OK;
+  const int64_t code = edges > capacity ? ETX_ERR_CAPACITY : ETX_ERR_UNSUPPORTED;
+  status[1] = edges;
+  set_status(status, code);
+  return code;
+}
+
 __global__ __launch_bounds__(256) void k_scan_top(int64_t* __restrict__ part, int64_t nb, int64_t* __restrict__ row_ptr,
                                                   int64_t n, int64_t capacity, int64_t* status) {
   if (status[0] != 0) return;
@@ -158,29 +192,89 @@ __global__ __launch_bounds__(256) void k_scan_top(int64_t* __restrict__ part, in
   }
   if (threadIdx.x == 0) {
     row_ptr[n] = carry;
-    if (carry > capacity) {
-      status[1] = carry;
-      set_status(status, ETX_ERR_CAPACITY);
-    } else if (carry >= 0x7fffffffLL) {
-      status[1] = carry;
-      set_status(status, ETX_ERR_UNSUPPORTED);
+    check_edges(carry, capacity, status);
+  }
+}
+
+// Row offsets of the kScanBlock counts from i0 on, eight consecutive counts per
+// thread of a 1024-thread workgroup, starting at `carry`, which moves past them.
+// One barrier: `tot` holds two slots that alternate between calls.
+constexpr int kScanThreads = 1024;
+static_assert(kScanBlock == 8 * kScanThreads, "eight counts per thread");
+
+__device__ inline void scan_counts(const int32_t* __restrict__ cnt, int64_t i0, int64_t n, int64_t* __restrict__ row_ptr,
+                                   int64_t& carry, int (&tot)[2][kScanThreads / 64], int slot) {
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int64_t i = i0 + (int64_t)t * 8;
+  int v[8] = {};
+  if (i + 8 <= n) {
+    const int4 a = *reinterpret_cast<const int4*>(cnt + i), b = *reinterpret_cast<const int4*>(cnt + i + 4);
+    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+    v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+  } else if (i < n) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = i + u < n ? cnt[i + u] : 0;
+  }
+  int sum = 0;
+#pragma unroll
+  for (int u = 0; u < 8; ++u) sum += v[u];
+  const int inc = wave_inclusive_scan(sum);
+  if (lane == 63) tot[slot][wave] = inc;
+  __syncthreads();
+  const int of_wave = lane < kScanThreads / 64 ? tot[slot][lane] : 0;
+  const int waves = wave_inclusive_scan(of_wave);
+  int64_t at = carry + __shfl(waves - of_wave, wave) + inc - sum;
+  carry += __shfl(waves, kScanThreads / 64 - 1);
+  if (i + 8 <= n) {
+#pragma unroll
+    for (int u = 0; u < 8; u += 2) {
+      longlong2 r;
+      r.x = at;
+      r.y = at += v[u];
+      at += v[u + 1];
+      *reinterpret_cast<longlong2*>(row_ptr + i + u) = r;
+    }
+  } else if (i < n) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      if (i + u < n) row_ptr[i + u] = at;
+      at += v[u];
     }
   }
 }
 
-__global__ __launch_bounds__(256) void k_scan_down(const int32_t* __restrict__ cnt, int64_t n, const int64_t* __restrict__ part,
-                                                   int64_t* __restrict__ row_ptr, const int64_t* status) {
+__global__ __launch_bounds__(kScanThreads) void k_scan_down(const int32_t* __restrict__ cnt, int64_t n,
+                                                            const int64_t* __restrict__ part,
+                                                            int64_t* __restrict__ row_ptr, const int64_t* status) {
   if (status[0] != 0) return;
-  __shared__ int tmp[4];
+  __shared__ int tot[2][kScanThreads / 64];
   int64_t base = part[blockIdx.x];
-  for (int q = 0; q < kScanBlock / 256; ++q) {
-    int64_t i = (int64_t)blockIdx.x * kScanBlock + q * 256 + threadIdx.x;
-    int v = i < n ? cnt[i] : 0;
-    int total;
-    int ex = block_exclusive_scan(v, tmp, total);
-    if (i < n) row_ptr[i] = base + ex;
-    base += total;
+  scan_counts(cnt, (int64_t)blockIdx.x * kScanBlock, n, row_ptr, base, tot, 0);
+}
+
+// The whole scan of a small batch in one workgroup, with the capacity check and
+// the per-event edge offsets: three launches fewer.  Up to kSmallScan counts
+// (two blocks) that is the shorter way; what a small batch pays is latency (one
+// event 25 -> 6 us).
+constexpr int64_t kSmallScan = 2 * kScanBlock;
+
+__global__ __launch_bounds__(kScanThreads) void k_scan_small(const int32_t* __restrict__ cnt, int64_t n,
+                                                             int64_t* __restrict__ row_ptr, int64_t capacity,
+                                                             const int64_t* __restrict__ hit_off, int64_t n_events,
+                                                             int64_t* __restrict__ edge_off, int64_t* status) {
+  __shared__ int tot[2][kScanThreads / 64];
+  __shared__ int64_t bad;
+  if (status[0] != 0) return;
+  int64_t carry = 0;
+  int slot = 0;
+  for (int64_t i0 = 0; i0 < n; i0 += kScanBlock, slot ^= 1) scan_counts(cnt, i0, n, row_ptr, carry, tot, slot);
+  if (threadIdx.x == 0) {
+    row_ptr[n] = carry;
+    bad = check_edges(carry, capacity, status);
   }
+  __syncthreads();
+  if (!edge_off || bad) return;
+  for (int64_t e = threadIdx.x; e <= n_events; e += kScanThreads) edge_off[e] = row_ptr[hit_off[e]];
 }
 
 __global__ void k_edge_off(const int64_t* __restrict__ hit_off, int64_t n_events, const int64_t* __restrict__ row_ptr,
@@ -194,10 +288,34 @@ __global__ void k_edge_off(const int64_t* __restrict__ hit_off, int64_t n_events
 // CSC: edge ids ordered by (dst, src), per event
 // --------------------------------------------------------------------------
 
-// Long rows (at least kCscRowWalk edges per source on average) are placed a
-// row per step by one wave; short rows by the whole block through LDS cursors
-// with a sort of every column afterwards (place = 1), or 64 edges per step by
-// one wave (place = 0).  All keep (dst, src) order.
+// The permutation of an event is built by one workgroup, in (dst, src) order
+// whichever way:
+//
+// - Walk (long rows, at least kCscRowWalk edges per source on average): the
+//   rows are cut into contiguous ranges, one per wave, each with its own LDS
+//   cursor per target.  The waves count their edges per target, a scan over
+//   (target, range) turns the counts into cursors, and every wave walks its
+//   rows in order, a row per step (the targets of a row are distinct, so its
+//   lanes never share a cursor).  The chain of LDS updates of one wave is what
+//   bounds it, so as many waves as the cursors leave room for: kCscWords / n,
+//   at most sixteen (one wave per event before: one dense 481-hit event 82 ->
+//   16 us, 20 full-size events 0.55 -> 0.17 ms, 1000 uneven dense events 2.5 ->
+//   1.4 ms; 1000 full-size events 1.46 -> 1.41 ms, bound by scattered 4-byte
+//   writes).
+// - Place (short rows): every thread drops edges into their columns through
+//   LDS cursors, any order within a column, then every column is sorted by edge
+//   index, which is source order (insertion sort: fewer than kCscRowWalk edges
+//   per column on average; 10,000 uneven events of a trained network 1.11 ->
+//   0.66 ms with the wide kernel for the events of over 4,096 hits).
+//
+// Events of few rows and edges in a batch with more events than the chip holds
+// are placed by small workgroups in memory (k_csc_place); all others by
+// 1024-thread workgroups with kCscWords of LDS (k_csc_wide), which place in LDS,
+// as many columns at a time as fit beside the cursors, and rank every edge within its column instead of
+// sorting columns (a column of sixty is then sixty short loops, not one long
+// one).  Both kernels are launched, each skips the
+// other's events; a batch of few events (at most one per CU) takes the wide
+// kernel alone, since it then waits for the latency of one event.
 constexpr int kCscRowWalk = 16;
 
 // The per-event kernels that keep one LDS word per hit of the event run as
@@ -213,18 +331,22 @@ __device__ inline bool event_in_launch(int n) {
   return CAP == kSmallEventHits ? n <= kSmallEventHits : n > kSmallEventHits;
 }
 
-template <int CAP>
-__global__ __launch_bounds__(256) void k_csc(const int64_t* __restrict__ hit_off, const int64_t* __restrict__ row_ptr,
-                                             const int32_t* __restrict__ dst, int64_t* __restrict__ col_ptr,
-                                             int32_t* __restrict__ csc, int place, const int64_t* status) {
+__device__ inline bool csc_small(int n, int64_t edges) {
+  return n <= kSmallEventHits && edges < (int64_t)kCscRowWalk * n;
+}
+
+__global__ __launch_bounds__(256) void k_csc_place(const int64_t* __restrict__ hit_off,
+                                                   const int64_t* __restrict__ row_ptr,
+                                                   const int32_t* __restrict__ dst, int64_t* __restrict__ col_ptr,
+                                                   int32_t* __restrict__ csc, const int64_t* status) {
   if (status[0] != 0) return;
-  __shared__ int cur[CAP];
+  __shared__ int cur[kSmallEventHits];
   __shared__ int tmp[4];
-  const int ev = blockIdx.x, t = threadIdx.x, lane = t & 63;
+  const int ev = blockIdx.x, t = threadIdx.x;
   const int64_t a = hit_off[ev];
   const int n = (int)(hit_off[ev + 1] - a);
-  if (!event_in_launch<CAP>(n)) return;
   const int64_t eb = row_ptr[a], ee = row_ptr[a + n];
+  if (!csc_small(n, ee - eb)) return;
   for (int i = t; i < n; i += 256) cur[i] = 0;
   __syncthreads();
   for (int64_t q = eb + t; q < ee; q += 256) atomicAdd(&cur[dst[q] - a], 1);
@@ -243,93 +365,171 @@ __global__ __launch_bounds__(256) void k_csc(const int64_t* __restrict__ hit_off
   }
   if (t == 0) col_ptr[a + n] = ee;
   __syncthreads();
-  if (place && ee - eb < (int64_t)kCscRowWalk * n) {
-    // short rows, whole block: every thread drops its edges into their columns
-    // through the LDS cursors (any order within a column), then every column
-    // is sorted by edge index, which is source order (insertion sort: fewer
-    // than kCscRowWalk edges per column on average).
-    for (int64_t q = eb + t; q < ee; q += 256) {
-      const int pos = atomicAdd(&cur[dst[q] - (int)a], 1);
-      csc[eb + pos] = (int32_t)q;
+  for (int64_t q = eb + t; q < ee; q += 256) {
+    const int pos = atomicAdd(&cur[dst[q] - (int)a], 1);
+    csc[eb + pos] = (int32_t)q;
+  }
+  __syncthreads();
+  for (int i = t; i < n; i += 256) {
+    const int64_t c0 = col_ptr[a + i], c1 = col_ptr[a + i + 1];
+    for (int64_t j = c0 + 1; j < c1; ++j) {
+      const int32_t v = csc[j];
+      int64_t k = j - 1;
+      for (; k >= c0; --k) {
+        const int32_t u = csc[k];
+        if (u < v) break;
+        csc[k + 1] = u;
+      }
+      csc[k + 1] = v;
     }
+  }
+}
+
+constexpr int kCscThreads = 1024, kCscWaves = kCscThreads / 64;
+constexpr int kCscWords = 32768;                  // 128 KiB: two cursors per hit of the largest event
+static_assert(kCscWords >= 2 * ETX_MAX_EVENT_HITS, "two ranges of the largest event");
+
+// place: short rows may be placed; every_event: the place kernel is not launched
+__global__ __launch_bounds__(kCscThreads) void k_csc_wide(const int64_t* __restrict__ hit_off,
+                                                          const int64_t* __restrict__ row_ptr,
+                                                          const int32_t* __restrict__ dst,
+                                                          int64_t* __restrict__ col_ptr, int32_t* __restrict__ csc,
+                                                          int place, int every_event, const int64_t* status) {
+  extern __shared__ int cur[];                    // [ranges][n] cursors, or n cursors and the placed edges
+  __shared__ int tot[2][kCscWaves];
+  if (status[0] != 0) return;
+  const int ev = blockIdx.x, t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int64_t a = hit_off[ev];
+  const int n = (int)(hit_off[ev + 1] - a);
+  const int64_t eb = row_ptr[a], ee = row_ptr[a + n];
+  const int64_t edges = ee - eb;
+  if (!every_event && place && csc_small(n, edges)) return;
+  if (n == 0) {
+    if (t == 0) col_ptr[a] = ee;
+    return;
+  }
+  const bool placed = place && edges < (int64_t)kCscRowWalk * n;
+  const int R = placed ? 1 : min(kCscWaves, kCscWords / n);
+  const int per = (n + R - 1) / R;                // rows per range
+  for (int i = t; i < R * n; i += kCscThreads) cur[i] = 0;
+  __syncthreads();
+  // counts per (range, target)
+  if (placed) {
+    for (int64_t q = eb + t; q < ee; q += kCscThreads) atomicAdd(&cur[dst[q] - (int)a], 1);
+  } else if (wave < R) {
+    const int64_t q1 = row_ptr[a + min(n, (wave + 1) * per)];
+    int* c = cur + wave * n;
+    constexpr int kBatch = 8;
+    for (int64_t q = row_ptr[a + min(n, wave * per)] + lane; q < q1; q += 64 * kBatch) {
+      int d[kBatch];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) d[u] = q + 64 * u < q1 ? dst[q + 64 * u] - (int)a : -1;
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u)
+        if (d[u] >= 0) atomicAdd(&c[d[u]], 1);
+    }
+  }
+  __syncthreads();
+  // exclusive scan over targets, and over the ranges of a target
+  int base = 0, slot = 0;
+  for (int i0 = 0; i0 < n; i0 += kCscThreads, slot ^= 1) {
+    const int i = i0 + t;
+    int sum = 0;
+    if (i < n)
+      for (int w = 0; w < R; ++w) sum += cur[w * n + i];
+    const int inc = wave_inclusive_scan(sum);
+    if (lane == 63) tot[slot][wave] = inc;
     __syncthreads();
-    for (int i = t; i < n; i += 256) {
-      const int64_t c0 = col_ptr[a + i], c1 = col_ptr[a + i + 1];
-      for (int64_t j = c0 + 1; j < c1; ++j) {
-        const int32_t v = csc[j];
-        int64_t k = j - 1;
-        for (; k >= c0; --k) {
-          const int32_t u = csc[k];
-          if (u < v) break;
-          csc[k + 1] = u;
-        }
-        csc[k + 1] = v;
+    int at = base + inc - sum;
+#pragma unroll
+    for (int w = 0; w < kCscWaves; ++w) {
+      at += w < wave ? tot[slot][w] : 0;
+      base += tot[slot][w];
+    }
+    if (i < n) {
+      col_ptr[a + i] = eb + at;
+      for (int w = 0; w < R; ++w) {
+        const int c = cur[w * n + i];
+        cur[w * n + i] = at;
+        at += c;
       }
+    }
+  }
+  if (t == 0) col_ptr[a + n] = ee;
+  __syncthreads();
+  if (placed) {
+    // cursor i is the start of column i until its edges are placed, its end
+    // afterwards; as many columns at a time as their edges fit beside the cursors
+    int* list = cur + n;
+    const int room = kCscWords - n;
+    for (int lo = 0; lo < n;) {
+      const int begin = cur[lo];
+      int hi = n;
+      if ((int)edges - begin > room) {
+        int x = lo + 1;                           // the last i with cur[i] <= begin + room
+        for (int step = n - x; x < hi - 1; step = (hi - x) / 2) {
+          const int m = min(hi - 1, x + max(1, step));
+          if (cur[m] - begin <= room) x = m;
+          else hi = m;
+        }
+        hi = x;
+      }
+      const int end = hi < n ? cur[hi] : (int)edges;
+      __syncthreads();                            // every thread has read the starts
+      for (int64_t q = eb + t; q < ee; q += kCscThreads) {
+        const int d = dst[q] - (int)a;
+        if (d >= lo && d < hi) list[atomicAdd(&cur[d], 1) - begin] = (int)(q - eb);
+      }
+      __syncthreads();
+      // an edge's place is the number of smaller ones in its column
+      for (int j = t; j < end - begin; j += kCscThreads) {
+        const int e = list[j], d = dst[eb + e] - (int)a;
+        const int c0 = (d > lo ? cur[d - 1] : begin) - begin, c1 = cur[d] - begin;
+        int rank = 0;
+        for (int k = c0; k < c1; ++k) rank += list[k] < e ? 1 : 0;
+        csc[eb + begin + c0 + rank] = (int32_t)(eb + e);
+      }
+      __syncthreads();
+      lo = hi;
     }
     return;
   }
-  if (t >= 64) return;
-  if (ee - eb >= (int64_t)kCscRowWalk * n) {
-    // one wave walks the rows in source order; the targets of one row are
-    // distinct, so its lanes never share a cursor.  Row bounds and targets are
-    // loaded kRow rows ahead so that HBM latency overlaps the LDS updates.
-    constexpr int kRow = 8;
-    int64_t rb[kRow + 1];
-    int dd[kRow];
-    auto load_block = [&](int i0, int64_t (&b)[kRow + 1], int (&d)[kRow]) {
+  if (wave >= R) return;
+  // Row bounds and targets are loaded kRow rows ahead so that their latency
+  // overlaps the LDS updates.
+  constexpr int kRow = 8;
+  const int r0 = min(n, wave * per), r1 = min(n, r0 + per);
+  int* c = cur + wave * n;
+  int64_t rb[kRow + 1];
+  int dd[kRow];
+  auto load_block = [&](int i0, int64_t (&b)[kRow + 1], int (&d)[kRow]) {
 #pragma unroll
-      for (int q = 0; q <= kRow; ++q) b[q] = row_ptr[a + min(i0 + q, n)];
+    for (int q = 0; q <= kRow; ++q) b[q] = row_ptr[a + min(i0 + q, r1)];
 #pragma unroll
-      for (int q = 0; q < kRow; ++q) d[q] = (b[q] + lane < b[q + 1]) ? dst[b[q] + lane] : 0;
-    };
-    if (n > 0) load_block(0, rb, dd);
-    for (int i0 = 0; i0 < n; i0 += kRow) {
-      int64_t nb[kRow + 1];
-      int nd[kRow];
-      if (i0 + kRow < n) load_block(i0 + kRow, nb, nd);
+    for (int q = 0; q < kRow; ++q) d[q] = (b[q] + lane < b[q + 1]) ? dst[b[q] + lane] : 0;
+  };
+  if (r0 < r1) load_block(r0, rb, dd);
+  for (int i0 = r0; i0 < r1; i0 += kRow) {
+    int64_t nb[kRow + 1];
+    int nd[kRow];
+    if (i0 + kRow < r1) load_block(i0 + kRow, nb, nd);
 #pragma unroll
-      for (int q = 0; q < kRow; ++q) {
-        if (rb[q] + lane < rb[q + 1]) {
-          const int dl = dd[q] - (int)a;
-          const int pos = cur[dl];
-          cur[dl] = pos + 1;
-          csc[eb + pos] = (int32_t)(rb[q] + lane);
-        }
-        wave_sync();
+    for (int q = 0; q < kRow; ++q) {
+      if (rb[q] + lane < rb[q + 1]) {
+        const int dl = dd[q] - (int)a;
+        const int pos = c[dl];
+        c[dl] = pos + 1;
+        csc[eb + pos] = (int32_t)(rb[q] + lane);
       }
-      if (i0 + kRow < n) {
-#pragma unroll
-        for (int q = 0; q <= kRow; ++q) rb[q] = nb[q];
-#pragma unroll
-        for (int q = 0; q < kRow; ++q) dd[q] = nd[q];
-      }
+      wave_sync();
     }
-    return;
-  }
-  // one wave scatters the edges in source-major order, 64 at a time: a lane's
-  // rank among the lanes of the chunk with the same target (lower lanes are
-  // earlier edges) gives its slot after the target's cursor, and the last of
-  // them advances the cursor, so every column keeps source order.  The next
-  // chunk's targets load while this one is placed.
-  int dn = eb + lane < ee ? dst[eb + lane] - (int)a : -1;
-  for (int64_t q0 = eb; q0 < ee; q0 += 64) {
-    const int64_t q = q0 + lane;
-    const int d = dn;
-    dn = q + 64 < ee ? dst[q + 64] - (int)a : -1;
-    int rank = 0, cnt = 0;
+    if (i0 + kRow < r1) {
 #pragma unroll
-    for (int k = 0; k < 64; ++k) {
-      const int o = __builtin_amdgcn_readlane(d, k);
-      cnt += o == d ? 1 : 0;
-      rank += (o == d && k < lane) ? 1 : 0;
+      for (int q = 0; q <= kRow; ++q) rb[q] = nb[q];
+#pragma unroll
+      for (int q = 0; q < kRow; ++q) dd[q] = nd[q];
     }
-    const int pos = d >= 0 ? cur[d] + rank : 0;
-    wave_sync();
-    if (d >= 0) {
-      csc[eb + pos] = (int32_t)q;
-      if (rank == cnt - 1) cur[d] = pos + 1;
-    }
-    wave_sync();
   }
 }
 
@@ -492,13 +692,19 @@ hipError_t launch_scan_counts(const RunArgs& a, bool candidates) {
   const int64_t nb = a.L.n_scan_blocks;
   int64_t* part = WS(a, scan_tmp, int64_t);
   int64_t* row_ptr = candidates ? WS(a, pf_tmp, int64_t) : WS(a, row_ptr, int64_t);
+  if (n <= kSmallScan) {
+    hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(kScanThreads), 0, a.stream, WS(a, cnt, int32_t), n, row_ptr,
+                       a.out.edge_capacity, a.hits.hit_off, a.hits.n_events, candidates ? nullptr : a.out.edge_off,
+                       a.out.status);
+    return hipGetLastError();
+  }
   if (nb > 0)
     hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(256), 0, a.stream, WS(a, cnt, int32_t), n, part,
                        a.out.status);
   hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(256), 0, a.stream, part, nb, row_ptr, n, a.out.edge_capacity,
                      a.out.status);
   if (nb > 0)
-    hipLaunchKernelGGL(k_scan_down, dim3((unsigned)nb), dim3(256), 0, a.stream, WS(a, cnt, int32_t), n, part, row_ptr,
+    hipLaunchKernelGGL(k_scan_down, dim3((unsigned)nb), dim3(kScanThreads), 0, a.stream, WS(a, cnt, int32_t), n, part, row_ptr,
                        a.out.status);
   if (!candidates) {
     int64_t ne = a.hits.n_events + 1;
@@ -510,13 +716,15 @@ hipError_t launch_scan_counts(const RunArgs& a, bool candidates) {
 
 hipError_t launch_csc(const RunArgs& a) {
   if (a.hits.n_events == 0) return hipSuccess;
-#define CSC(C_)                                                                                           \
-  hipLaunchKernelGGL(k_csc<C_>, dim3((unsigned)a.hits.n_events), dim3(256), 0, a.stream, a.hits.hit_off,  \
-                     WS(a, row_ptr, int64_t), a.out.dst, WS(a, col_ptr, int64_t), WS(a, csc, int32_t),     \
-                     a.ctx->csc_place, a.out.status)
-  CSC(kSmallEventHits);
-  CSC(ETX_MAX_EVENT_HITS);
-#undef CSC
+  const dim3 grid((unsigned)a.hits.n_events);
+  const int place = a.ctx->csc_place;
+  const bool wide_only = !place || a.hits.n_events <= a.ctx->n_cu;
+  if (!wide_only)
+    hipLaunchKernelGGL(k_csc_place, grid, dim3(256), 0, a.stream, a.hits.hit_off, WS(a, row_ptr, int64_t), a.out.dst,
+                       WS(a, col_ptr, int64_t), WS(a, csc, int32_t), a.out.status);
+  hipLaunchKernelGGL(k_csc_wide, grid, dim3(kCscThreads), sizeof(int) * kCscWords, a.stream, a.hits.hit_off,
+                     WS(a, row_ptr, int64_t), a.out.dst, WS(a, col_ptr, int64_t), WS(a, csc, int32_t), place,
+                     wide_only ? 1 : 0, a.out.status);
   return hipGetLastError();
 }
 
@@ -543,6 +751,7 @@ hipError_t launch_union_find(const RunArgs& a) {
 int graph_attributes(size_t max_lds) {
   int bad = 0;
   bad |= hipFuncSetAttribute(reinterpret_cast<const void*>(k_bucket), hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_lds) != hipSuccess;
+  bad |= hipFuncSetAttribute(reinterpret_cast<const void*>(k_csc_wide), hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_lds) != hipSuccess;
   return bad;
 }
 
