@@ -68,3 +68,29 @@ def test_graph_kernels_at_sizes(sizes, k_max, least, place):
     big = int(np.argmax(sizes))
     per_hit = (row_ptr[ho[big + 1]] - row_ptr[ho[big]]) / max(sizes[big], 1)
     assert per_hit >= least, per_hit
+
+
+@pytest.mark.parametrize("sizes,kept", [
+    ([300], "all"), ([300], "few"), ([4096], "all"), ([4097], "few"), ([4097], "all"), ([16384, 0, 7], "few"),
+    (MANY, "all"), (MANY + [4097, 0, 4500], "few"), (MANY + [4097, 0, 4500], "all")])
+def test_components_at_sizes(sizes, kept):
+    """Component labels when every edge is kept and when about a fifth is."""
+    from oracle import oracle as O
+    from paper_2508_07423_amd import etx
+    batch = _batch(sizes)
+    b = etx.to_device(batch)
+    w = synth.C1.with_(k_max=8)
+    weights = synth.xavier_weights(w)
+    p = etx.Pipeline(w, weights)
+    p.run(b)
+    score = p.results(b)["score"]
+    p.close()
+    thr = float(np.float32(score.min() if kept == "all" else np.quantile(score, 0.8)))
+    p = etx.Pipeline(w.with_(threshold=thr), weights)
+    p.run(b)
+    res = p.results(b)
+    p.close()
+    keep = res["score"] >= np.float32(thr)
+    share = keep.mean()
+    assert share == 1 if kept == "all" else 0.1 < share < 0.3
+    assert np.array_equal(res["labels"], O.components(b.n_hits, res["src"], res["dst"], keep))
