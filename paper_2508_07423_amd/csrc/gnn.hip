@@ -13,8 +13,9 @@
 // computed once per node in the node kernels and gathered per edge, so the
 // per-edge work is one H x H product per layer.  Messages are atomic-free
 // segmented sums: the out-sums (runs of the source-major edge list) are
-// reduced in registers by the kernels that write the edge encodings, the
-// in-sums gathered through the (dst, src)-ordered CSC permutation.
+// reduced in registers by the kernels that write the edge encodings (or, short
+// rows with the compact state, by the node kernel), the in-sums gathered through
+// the (dst, src)-ordered CSC permutation.
 //
 // Every MLP kernel is instantiated for the GEMM operand precision P (FP32,
 // BF16, FP8-E4M3 with per-tensor power-of-two scales).  Accumulation,
@@ -72,6 +73,7 @@ struct GnnArgs {
   int step;
   int xcd_map;              // 1: logical workgroup ids contiguous per XCD
   int keep_final;           // 1: the final edge step also stores e_S (the triplet classifiers' input)
+  int gather_out;           // 1: the node kernel sums short out-rows itself (own_out_sums)
   const int64_t* status;
 };
 
@@ -86,6 +88,26 @@ __device__ inline int64_t logical_block(const GnnArgs& A) {
   const int64_t G = gridDim.x, b = blockIdx.x;
   if (!A.xcd_map || G % kXcds != 0) return b;
   return (b % kXcds) * (G / kXcds) + b / kXcds;
+}
+
+// Where the messages are gathered in the node kernel, the out-sums of short
+// rows are too: a node's out-edges are a few consecutive rows of the edge list,
+// which the node kernel's in-sums read anyway (as in-edges of hits one or two
+// planes on, from the same XCD's L2), and the edge kernels neither reduce nor
+// write the out-sums and their partials (4 H bytes per hit and 4 H per 8 edges
+// written, and read again).  Measured at 10,000 uneven events of a trained
+// network, BF16 state, 1.9 edges per hit: edge encoder and edge steps 6.9 ->
+// 5.2 ms per pass, node steps 6.4 -> 6.1 ms.  With FP32 rows the second read
+// costs what the edge kernels gain (20.5 + 12.7 against 22.2 + 11.2 ms), and
+// long rows are read twice from memory, so FP32 state and more than kOwnRow
+// edges per hit keep the edge kernels' sums.  Both kernels decide on the same
+// two numbers.  Hidden size 32 only: at 64 the rows in flight do not fit the
+// registers beside the network's inputs.
+constexpr int kOwnRow = 6;
+template <int H, int P>
+constexpr bool kOwnForm = H == 32 && StorePrec<P>::value != P_F32;
+__device__ inline bool own_out_sums(const GnnArgs& A, int64_t edges) {
+  return A.gather_out && edges < kOwnRow * A.n_hits;
 }
 
 __device__ inline void stage_bytes(char* dst, const char* src, int n) {
@@ -641,6 +663,7 @@ __global__ __launch_bounds__(512) void k_edge_encode(GnnArgs A) {
   const float s_ee2 = asc(A, Q_EE2), o_ee2 = s_ee2 * wsc(A, SW_EE2);
   const float s_e0 = asc(A, Q_E + 0), inv_e0 = 1.0f / s_e0;
   const int64_t E = A.row_ptr[A.n_hits];
+  const bool own = kOwnForm<H, P> && own_out_sums(A, E);
   const int64_t ntiles = (E + kCols - 1) / kCols;
   const int64_t stride = (int64_t)gridDim.x * nw;
   EdgeFeed<P, H, PIPE, GH && kHalfH<P>> feed{A.src, A.dst, nullptr, GH ? A.h : A.ps, GH ? A.h : A.pd, E, stride, lane & 15};
@@ -692,6 +715,7 @@ __global__ __launch_bounds__(512) void k_edge_encode(GnnArgs A) {
     ln_relu<H>(o);
     observe<H / 4>(A.calib, SC_GNN + Q_E, o, valid);
     store_e<P, H, true>(A.e, col, o, valid, inv_e0, s_e0, o);
+    if (own) continue;
     if constexpr (OL)
       out_sums_lds<H>(A, tile, ti, key, o, reinterpret_cast<float*>(w + off) + wave * kOutBufFloats);
     else
@@ -832,30 +856,79 @@ __device__ inline void fetch_msg_idx(const GnnArgs& A, int64_t node, bool valid,
   for (int u = 0; u < U; ++u) m.id0[u] = m.cb + u < m.ce ? A.csc[m.cb + u] : -1;
 }
 
-// Messages of a node gathered in the node kernel: the out-sum from the edge
-// kernels' tile partials (as k_segsum), the in-sum over the CSC rows in CSC
-// order, so the sums are bit-identical to k_segsum's.
+// The sum of up to four consecutive edge rows before `end` (not before `begin`),
+// (last + one before) + (two before + three before), missing rows as zeros.
 template <int H, int P>
-__device__ inline void gather_messages(const GnnArgs& A, int64_t node, bool valid, const MsgIdx<H, P>& m, float* mo,
-                                       float* mi) {
+__device__ inline void quad_sum(float* s, const GnnArgs& A, int64_t begin, int64_t end, float scale) {
+  RawE<P, H> raw[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    if (end - 1 - u >= begin) fetch_e<P, H>(raw[u], A.e, end - 1 - u);
+    else
+#pragma unroll
+      for (int q = 0; q < ELayout<P, H>::NQ; ++q) raw[u].v[q] = make_uint4(0u, 0u, 0u, 0u);
+  }
+  float v[H / 4], w[H / 4];
+  decode_e<P, H>(s, raw[0], scale);
+  decode_e<P, H>(v, raw[1], scale);
+#pragma unroll
+  for (int r = 0; r < H / 4; ++r) s[r] += v[r];
+  decode_e<P, H>(v, raw[2], scale);
+  decode_e<P, H>(w, raw[3], scale);
+#pragma unroll
+  for (int r = 0; r < H / 4; ++r) s[r] += v[r] + w[r];
+}
+
+// The out-sum of edges [rb, re), as the edge kernels' segmented scan gives it: a
+// tile's part of the row is a binary tree from its last edge (a scan's value at
+// the end of a run of 2^k or fewer columns), tiles' parts are added in order.
+template <int H, int P>
+__device__ inline void own_out_sum(const GnnArgs& A, int64_t rb, int64_t re, float* mo) {
+  const float scale = P == P_FP8 ? asc(A, Q_E + A.step) : 1.0f;
+  for (int64_t b = rb; b < re;) {
+    const int64_t e = min(re, (b / kCols + 1) * kCols);
+    float s[H / 4], t[H / 4], q[H / 4];
+    quad_sum<H, P>(s, A, b, e, scale);
+    if (e - b > 4) {
+      quad_sum<H, P>(q, A, b, e - 4, scale);
+#pragma unroll
+      for (int r = 0; r < H / 4; ++r) s[r] += q[r];
+      if (e - b > 8) {
+        quad_sum<H, P>(t, A, b, e - 8, scale);
+        if (e - b > 12) {
+          quad_sum<H, P>(q, A, b, e - 12, scale);
+#pragma unroll
+          for (int r = 0; r < H / 4; ++r) t[r] += q[r];
+        }
+#pragma unroll
+        for (int r = 0; r < H / 4; ++r) s[r] += t[r];
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < H / 4; ++r) mo[r] += s[r];
+    b = e;
+  }
+}
+
+// Messages of a node gathered in the node kernel: the out-sum from its own rows
+// (own) or the edge kernels' tile partials (as k_segsum), the in-sum over the
+// CSC rows in CSC order, so the sums are bit-identical to k_segsum's.
+template <int H, int P>
+__device__ inline void gather_messages(const GnnArgs& A, int64_t node, bool valid, const MsgIdx<H, P>& m, bool own,
+                                       float* mo, float* mi) {
   constexpr int U = kGatherU<H, P>;
 #pragma unroll
   for (int r = 0; r < H / 4; ++r) mo[r] = mi[r] = 0.f;
   if (!valid) return;
   const int64_t rb = m.rb, re = m.re, cb = m.cb, ce = m.ce;
-  if (re > rb) {
-    const int64_t t0 = rb / kCols, t1 = (re - 1) / kCols;
-    if (t0 == t1) {
-      load_cols<H>(mo, A.msg + node * 2 * H, true);
-    } else {
-      for (int64_t i = 0; i <= t1 - t0; ++i) add_cols<H>(mo, A.opart + ((t0 + i) * 2 + (i == 0 ? 1 : 0)) * H, true);
-    }
-  }
   int id[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) id[u] = m.id0[u];
-  for (int64_t t = cb; t < ce; t += U) {
-    RawE<P, H> raw[U];
+  // the first in-rows are in flight while the out-sum is formed (FP32 rows take
+  // too many registers for that)
+  constexpr bool AHEAD = StorePrec<P>::value != P_F32;
+  RawE<P, H> raw[U];
+  auto fetch_in = [&]() {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (id[u] >= 0) fetch_e<P, H>(raw[u], A.e, id[u]);
@@ -863,6 +936,20 @@ __device__ inline void gather_messages(const GnnArgs& A, int64_t node, bool vali
 #pragma unroll
         for (int q = 0; q < ELayout<P, H>::NQ; ++q) raw[u].v[q] = make_uint4(0u, 0u, 0u, 0u);
     }
+  };
+  if constexpr (AHEAD) fetch_in();
+  if (kOwnForm<H, P> && own) {
+    own_out_sum<H, P>(A, rb, re, mo);
+  } else if (re > rb) {
+    const int64_t t0 = rb / kCols, t1 = (re - 1) / kCols;
+    if (t0 == t1) {
+      load_cols<H>(mo, A.msg + node * 2 * H, true);
+    } else {
+      for (int64_t i = 0; i <= t1 - t0; ++i) add_cols<H>(mo, A.opart + ((t0 + i) * 2 + (i == 0 ? 1 : 0)) * H, true);
+    }
+  }
+  for (int64_t t = cb; t < ce; t += U) {
+    if constexpr (!AHEAD) fetch_in();
     // the next ids load while these rows are in flight
 #pragma unroll
     for (int u = 0; u < U; ++u) id[u] = t + U + u < ce ? A.csc[t + U + u] : -1;
@@ -872,6 +959,9 @@ __device__ inline void gather_messages(const GnnArgs& A, int64_t node, bool vali
       decode_e<P, H>(v, raw[u], 1.0f);
 #pragma unroll
       for (int r = 0; r < H / 4; ++r) mi[r] += v[r];
+    }
+    if constexpr (AHEAD) {
+      if (t + U < ce) fetch_in();
     }
   }
   if constexpr (P == P_FP8) {
@@ -901,6 +991,7 @@ __global__ __launch_bounds__(NodeThreads<P>::value) void k_node_step(GnnArgs A) 
   const float w1s = wsc(A, SW_STEP + 4 * k), w2s = wsc(A, SW_STEP + 4 * k + 1), wes = wsc(A, SW_STEP + 4 * k + 2);
   const int64_t ntiles = (A.n_hits + kCols - 1) / kCols;
   const int64_t stride = (int64_t)gridDim.x * nw;
+  const bool own = FUSE && kOwnForm<H, P> && own_out_sums(A, A.row_ptr[A.n_hits]);
   // with fused messages the next tile's message indices load a tile ahead
   MsgIdx<H, P> mnext;
   int64_t tile = logical_block(A) * nw + wave;
@@ -917,7 +1008,7 @@ __global__ __launch_bounds__(NodeThreads<P>::value) void k_node_step(GnnArgs A) 
       const MsgIdx<H, P> m = mnext;
       const int64_t cn = (tile + stride) * kCols + (lane & 15);
       fetch_msg_idx<H, P>(A, cn, tile + stride < ntiles && cn < A.n_hits, mnext);
-      gather_messages<H, P>(A, col, valid, m, x + H / 4, x + H / 2);
+      gather_messages<H, P>(A, col, valid, m, own, x + H / 4, x + H / 2);
     } else {
       load_cols<H>(x + H / 4, A.msg + col * 2 * H, valid);
       load_cols<H>(x + H / 2, A.msg + col * 2 * H + H, valid);
@@ -996,6 +1087,7 @@ __global__ __launch_bounds__(512) void k_edge_step(GnnArgs A) {
   const float s_e = asc(A, Q_E + k), s_en2 = asc(A, Q_EN2), s_next = asc(A, Q_E + k + 1);
   const float w1s = wsc(A, SW_STEP + 4 * k + 2), w2s = wsc(A, SW_STEP + 4 * k + 3), wcs = wsc(A, SW_CLS1);
   const int64_t E = A.row_ptr[A.n_hits];
+  const bool own = kOwnForm<H, P> && own_out_sums(A, E);
   const int64_t ntiles = (E + kCols - 1) / kCols;
   const int64_t stride = (int64_t)gridDim.x * nw;
   EdgeFeed<P, H, PIPE, GH && kHalfH<P>> feed{A.src, A.dst, A.e, GH ? A.h : A.ps, GH ? A.h : A.pd, E, stride, lane & 15};
@@ -1082,6 +1174,7 @@ __global__ __launch_bounds__(512) void k_edge_step(GnnArgs A) {
     observe<H / 4>(A.calib, SC_GNN + Q_E + k + 1, o, valid);
     if (!FINAL) {
       store_e<P, H>(A.e, col, o, valid, 1.0f / s_next, s_next, o);
+      if (own) continue;
       if constexpr (OL)
         out_sums_lds<H>(A, tile, ti, key, o, reinterpret_cast<float*>(w + off) + wave * kOutBufFloats);
       else
@@ -1135,6 +1228,7 @@ static GnnArgs gnn_args(const RunArgs& a) {
   A.sc = c->dev_scales + (a.prec == P_I8M ? SC_I8 : 0);   // the INT8 scale set
   A.xcd_map = a.ctx->xcd_map;
   A.keep_final = a.keep_final_e ? 1 : 0;
+  A.gather_out = c->fuse_messages;
   A.status = a.out.status;
   return A;
 }
