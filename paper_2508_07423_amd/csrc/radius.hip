@@ -3,12 +3,13 @@
 // planes p+1 .. p+window whose squared embedding distance is below r^2,
 // keeping at most k_max per source: the k_max smallest by (d^2, target index).
 //
-// One workgroup per (event, source plane).  The candidate window (hits of the
+// One workgroup per (event, source plane), or several that share its sources
+// where the batch has few.  The candidate window (hits of the
 // next planes) is staged in LDS and binned along its widest embedding axis into
 // cells about r wide (a counting sort), a one-dimensional cell list: a source
 // only scans the cells its coordinate on that axis reaches within r, which is
 // exact because a distance below r bounds every coordinate difference.  Sources
-// with few candidates are handled four to a wave; otherwise each wave handles one source
+// with few candidates are handled eight to a wave; otherwise each wave handles one source
 // at a time: in-radius candidates are compacted into an LDS list with a wave
 // ballot and prefix count, the k_max boundary is found by a radix select on
 // the float bits of d^2 (ties at the boundary resolved by the target index), and
@@ -20,10 +21,7 @@ namespace etx {
 
 namespace {
 
-constexpr int kRadiusThreads = 512;     // 8 waves
-constexpr int kRadiusWaves = kRadiusThreads / 64;
 constexpr int kList = 256;              // per-wave list of in-radius candidates
-constexpr int kCells = 256;             // most cells of a window's cell list
 
 __device__ inline void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -39,8 +37,9 @@ struct RadiusArgs {
   int n_planes, window, k_max, dim;
   int stage_window;        // 0: always read the window from HBM
   int sort_min;            // staged windows of at least this many hits are sorted (cell list)
-  int fast;                // select pass: sources with at most 16 in-radius candidates take the 16-lane path
-  int split;               // 1: windows up to the small capacity go to the small-LDS launch, the rest to the other
+  int fast;                // select pass: sources with at most kFastList in-radius candidates take the fast path
+  int parts;               // workgroups that share a unit's sources (blockIdx.y takes every parts-th)
+  int split;               // > 0: windows of up to this many hits go to the small workgroups' launch, the rest to the other
   float r2, r;
   int32_t* cnt;            // count pass output (and the select pass's)
   const int64_t* row_ptr;  // emit pass input
@@ -66,17 +65,36 @@ __device__ inline float dist2(const float (&s)[DP], const float* c) {
   return d2;
 }
 
-// LDS capacity of the staged window for a padded embedding width DP.  The
-// SMALL form stages half as many hits: 48 KiB instead of 72 KiB at width 8,
-// so that three workgroups share a CU instead of two (at width 16 the
-// registers still allow only two).  A workgroup's few hundred distance
-// evaluations on a trained embedding wait mostly on memory latency (one
-// workgroup per CU instead of two nearly doubles the search time), so the
-// small windows gain from the third workgroup in flight.
-template <int DP, bool SMALL = false>
-struct RadiusLds {
-  static constexpr int cap = (DP <= 8 ? 1024 : 512) / (SMALL ? 2 : 1);
-  static constexpr size_t bytes = (size_t)cap * (DP * 4 + 12) + kRadiusWaves * (kList * 8 + 64 * 4 + 256 * 4) + 64;
+// The fast path's rows: a source on kFastRow lanes, kFastRows sources per wave.
+// A trained embedding leaves about twenty candidates in a source's cells and two
+// to three within r; most instructions are per round of a row (range, ranks,
+// stores), not per candidate, so eight sources per round beat four (trained
+// batches 1.09 -> 0.94 ms per 3,000 events, 16 of 8 lanes; 4 lanes the same).
+constexpr int kFastRow = 8, kFastRows = 64 / kFastRow;
+constexpr int kFastList = 16;           // most in-radius candidates of a source finished on the fast path
+static_assert(kFastRows * kFastList <= 256, "the rows' lists share the wave's histogram");
+
+// Workgroup shapes for a padded embedding width DP: waves, hits of a staged
+// window, most cells of its cell list.
+//   R_LARGE  eight waves, the largest windows (the only shape of unsplit launches)
+//   R_SMALL  four waves, windows of up to 256: with many candidates per source a
+//            workgroup's time is its sources in turn, and short units on small
+//            workgroups fill the chip more evenly (300 uneven dense events: 1.43
+//            ms; eight waves and 512 hits 1.54, four and 512 1.74)
+//   R_SMALL_FAST  four waves, windows of up to 512, for the fast path: few
+//            instructions per source, so the workgroup's fixed part (staging, cell
+//            list) counts (3,000 trained events: 0.94 ms; four and 256 1.00, eight
+//            and 512 1.06, two and 512 1.03, one and 256 1.26)
+enum RadiusForm { R_LARGE = 0, R_SMALL = 1, R_SMALL_FAST = 2 };
+
+template <int DP, int FORM>
+struct RadiusShape {
+  static constexpr int waves = FORM == R_LARGE ? 8 : 4;
+  static constexpr int threads = waves * 64;
+  static constexpr int cap = FORM == R_LARGE ? (DP <= 8 ? 1024 : 512) : FORM == R_SMALL ? 256 : 512;
+  static constexpr int cells = FORM == R_LARGE ? 256 : 64;
+  static constexpr size_t bytes =
+      (size_t)cap * (DP * 4 + 12) + cells * 4 + waves * (kList * 8 + 256 * 4) + 64;
 };
 
 // MODE: 0 counts the kept neighbours of every source; 1 writes them as CSR rows
@@ -105,19 +123,21 @@ __device__ inline int window_hits(const int32_t* po, int p, int P, int window) {
 
 // One (event, plane) unit: its sources against their candidate window.
 // Entered by the whole workgroup; every early return is workgroup-uniform.
-template <int MODE, int DP, bool SMALL>
-__device__ inline void radius_unit(const RadiusArgs& A, float* lds, int ev, int p) {
+template <int MODE, int DP, int FORM>
+__device__ inline void radius_unit(const RadiusArgs& A, float* lds, int ev, int p, int part) {
   constexpr bool EMIT = MODE != R_COUNT;
-  constexpr int CAP = RadiusLds<DP, SMALL>::cap;
+  using Shape = RadiusShape<DP, FORM>;
+  constexpr int CAP = Shape::cap, kRadiusThreads = Shape::threads, kRadiusWaves = Shape::waves,
+                kCells = Shape::cells;
   float* cemb = lds;                                              // [CAP][DP]
-  int* cj = reinterpret_cast<int*>(cemb + CAP * DP);              // [CAP] target hit index
-  float* skey = reinterpret_cast<float*>(cj + CAP);               // [CAP] cell ends, then hard sources
-  int* sidx = reinterpret_cast<int*>(skey + CAP);                 // [CAP] slots in cell order
-  float* ld2 = reinterpret_cast<float*>(sidx + CAP);              // [waves][kList]
+  int* cend = reinterpret_cast<int*>(cemb + CAP * DP);            // [kCells] cell ends
+  float* ld2 = reinterpret_cast<float*>(cend + kCells);           // [waves][kList]
   int* lj = reinterpret_cast<int*>(ld2 + kRadiusWaves * kList);   // [waves][kList]
-  int* sel = lj + kRadiusWaves * kList;                           // [waves][64]
-  int* hist = sel + kRadiusWaves * 64;                            // [waves][256] radix-select histogram
+  int* hist = lj + kRadiusWaves * kList;                          // [waves][256] radix-select histogram, then row buffer
   int* misc = hist + kRadiusWaves * 256;                          // [16]
+  int* cj = misc + 16;                                            // [CAP] target hit index
+  int* hard = cj + CAP;                                           // [CAP] sources for the one-wave path
+  int* sidx = hard + CAP;                                         // [CAP] slots in cell order
 
   const int P = A.n_planes;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -129,27 +149,29 @@ __device__ inline void radius_unit(const RadiusArgs& A, float* lds, int ev, int 
   const int s0 = po[p], s1 = po[p + 1];
   const int nwin = window_hits(po, p, P, A.window);
   if (status != 0) return;
-  const int nsrc = s1 - s0;
-  if (nsrc == 0) return;
+  // this workgroup's sources: number part, part + parts, ... of the unit
+  const int parts = A.parts, nsrc = (s1 - s0 - part + parts - 1) / parts;
+  if (nsrc <= 0) return;
+  const int32_t* sources = A.bucket + a + s0 + part;
   const int w0 = s1;
   // split launches: each unit goes to exactly one of the two
-  if (A.split && (SMALL ? nwin > CAP : nwin <= RadiusLds<DP, true>::cap)) return;
+  if (A.split && (FORM != R_LARGE ? nwin > CAP : nwin <= A.split)) return;
   const int32_t* wb = A.bucket + a + w0;
   const bool staged = A.stage_window && nwin <= CAP;
   // windows of at least sort_min hits get a cell list along their widest axis
   // and each source scans only the cells within reach; smaller ones are
   // scanned whole
   const bool sorted = staged && nwin >= A.sort_min;
-  // Fast path of the select pass over a staged window (below): four sources
+  // Fast path of the select pass over a staged window (below): kFastRows sources
   // per wave.  Each row's first source index is loaded now, beside the
   // window's, and its embedding row once the window is staged, so that both
   // arrive while the cell list is built; later sources are fetched one
   // iteration ahead.
-  const bool fast = MODE == R_SELECT && A.fast && staged && nsrc <= (sorted ? CAP - kCells : CAP);
-  const int sub = lane >> 4, l16 = lane & 15;
+  const bool fast = MODE == R_SELECT && A.fast && staged && nsrc <= CAP;
+  const int sub = lane / kFastRow, lr = lane % kFastRow;
   int32_t i_pf = 0;
   float4 e_pf[DP / 4];
-  if (fast && wave * 4 + sub < nsrc) i_pf = A.bucket[a + s0 + wave * 4 + sub];
+  if (fast && wave * kFastRows + sub < nsrc) i_pf = sources[(wave * kFastRows + sub) * parts];
   bool pf_done = false;
   auto prefetch_row = [&](bool live) {
 #pragma unroll
@@ -158,9 +180,8 @@ __device__ inline void radius_unit(const RadiusArgs& A, float* lds, int ev, int 
                      : make_float4(0.f, 0.f, 0.f, 0.f);
     pf_done = true;
   };
-  // cell list of a sorted window (in the key array's place): cend[k] ends up
-  // as the end of cell k in the slot order sidx
-  int* cend = reinterpret_cast<int*>(skey);
+  // cell list of a sorted window: cend[k] ends up as the end of cell k in the
+  // slot order sidx
   float cell_lo = 0.f, cell_inv = 0.f;
   int ncell = 1;
   auto cell_of = [&](float key) {
@@ -174,7 +195,7 @@ __device__ inline void radius_unit(const RadiusArgs& A, float* lds, int ev, int 
       for (int q = 0; q < DP; q += 4)
         *reinterpret_cast<float4*>(cemb + c * DP + q) = *reinterpret_cast<const float4*>(A.emb + (int64_t)j * kDpad + q);
     }
-    if (fast) prefetch_row(wave * 4 + sub < nsrc);
+    if (fast) prefetch_row(wave * kFastRows + sub < nsrc);
     __syncthreads();
   }
   if (sorted && nwin > 0) {
@@ -198,7 +219,7 @@ __device__ inline void radius_unit(const RadiusArgs& A, float* lds, int ev, int 
         lo[q + 3] = fminf(lo[q + 3], v.w); hi[q + 3] = fmaxf(hi[q + 3], v.w);
       }
     }
-    if (fast) prefetch_row(wave * 4 + sub < nsrc);
+    if (fast) prefetch_row(wave * kFastRows + sub < nsrc);
     // block max of each axis range through the per-wave lists (reused as scratch)
 #pragma unroll
     for (int k = 0; k < DP; ++k) {
@@ -297,23 +318,21 @@ __device__ inline void radius_unit(const RadiusArgs& A, float* lds, int ev, int 
   };
   float* wl2 = ld2 + wave * kList;
   int* wlj = lj + wave * kList;
-  int* sl = sel + wave * 64;
   int* hw = hist + wave * 256;
+  int* sl = hw;       // a source's kept targets: written once its histogram is done with
 
-  // Fast path of the select pass over a staged window: four sources per wave,
-  // one per 16-lane row, each over its own candidate range.  A source with at
+  // Fast path of the select pass over a staged window: a source per row of
+  // lanes, each over its own candidate range.  A source with at
   // most 16 in-radius candidates (and no k_max cut) is finished here: its
   // targets, ranked by index, are exactly what the full path keeps.  Other
-  // sources go to a list (the slot array of a scanned window, the key array
-  // past the cell ends of a sorted one) for the one-wave-per-source path.
-  int* hard = sorted ? cend + kCells : sidx;
+  // sources go to a list for the one-wave-per-source path.
   int nwork = nsrc;
   if (fast) {
-    if (!pf_done) prefetch_row(wave * 4 + sub < nsrc);
+    if (!pf_done) prefetch_row(wave * kFastRows + sub < nsrc);
     if (threadIdx.x == 0) misc[1] = 0;
     __syncthreads();
-    int* sb = sl + 16 * sub;
-    for (int s4 = wave * 4; s4 < nsrc; s4 += kRadiusWaves * 4) {
+    int* sb = sl + kFastList * sub;
+    for (int s4 = wave * kFastRows; s4 < nsrc; s4 += kRadiusWaves * kFastRows) {
       const int s = s4 + sub;
       const bool live = s < nsrc;
       const int32_t i = i_pf;
@@ -322,17 +341,17 @@ __device__ inline void radius_unit(const RadiusArgs& A, float* lds, int ev, int 
       for (int q = 0; q < DP / 4; ++q) {
         se[4 * q] = e_pf[q].x; se[4 * q + 1] = e_pf[q].y; se[4 * q + 2] = e_pf[q].z; se[4 * q + 3] = e_pf[q].w;
       }
-      const bool live_next = s + kRadiusWaves * 4 < nsrc;
-      i_pf = live_next ? A.bucket[a + s0 + s + kRadiusWaves * 4] : 0;
+      const bool live_next = s + kRadiusWaves * kFastRows < nsrc;
+      i_pf = live_next ? sources[(s + kRadiusWaves * kFastRows) * parts] : 0;
       int cb, ce;
       range(se, cb, ce);
-      // the longest of the four ranges (rows hold one value each)
+      // the longest of the rows' ranges (a row holds one value)
       int len = live ? ce - cb : 0;
-      len = max(len, __shfl_xor(len, 16));
-      len = max(len, __shfl_xor(len, 32));
+#pragma unroll
+      for (int d = kFastRow; d < 64; d <<= 1) len = max(len, __shfl_xor(len, d));
       int n = 0;
-      for (int c0 = 0; c0 < len; c0 += 16) {
-        const int c = cb + c0 + l16;
+      for (int c0 = 0; c0 < len; c0 += kFastRow) {
+        const int c = cb + c0 + lr;
         bool in = false;
         int j = 0;
         if (live && c < ce) {
@@ -340,25 +359,25 @@ __device__ inline void radius_unit(const RadiusArgs& A, float* lds, int ev, int 
           j = cj[slot];
           in = dist2<DP>(se, cemb + slot * DP) < A.r2;
         }
-        const uint32_t m = (uint32_t)(__ballot(in) >> (16 * sub)) & 0xffffu;
+        const uint32_t m = (uint32_t)(__ballot(in) >> (kFastRow * sub)) & ((1u << kFastRow) - 1u);
         if (in) {
-          const int pos = n + __popc(m & ((1u << l16) - 1u));
-          if (pos < 16) sb[pos] = j;
+          const int pos = n + __popc(m & ((1u << lr) - 1u));
+          if (pos < kFastList) sb[pos] = j;
         }
         n += __popc(m);
       }
       prefetch_row(live_next);
       wave_sync();
-      const bool done = live && n <= 16 && n <= A.k_max;
+      const bool done = live && n <= kFastList && n <= A.k_max;
       if (done) {
-        if (l16 < n) {
-          const int my = sb[l16];
+        for (int k = lr; k < n; k += kFastRow) {
+          const int my = sb[k];
           int rank = 0;
           for (int q = 0; q < n; ++q) rank += sb[q] < my;
           A.slots[slot_index(i, rank, A.n_hits, A.k_max)] = my;
         }
-        if (l16 == 0) A.cnt[i] = n;
-      } else if (live && l16 == 0) {
+        if (lr == 0) A.cnt[i] = n;
+      } else if (live && lr == 0) {
         hard[atomicAdd(&misc[1], 1)] = s;
       }
       wave_sync();
@@ -369,7 +388,7 @@ __device__ inline void radius_unit(const RadiusArgs& A, float* lds, int ev, int 
   auto source_of = [&](int h) { return fast ? hard[h] : h; };
 
   // the next source's index and embedding load while this one is processed
-  int32_t i_next = wave < nwork ? A.bucket[a + s0 + source_of(wave)] : 0;
+  int32_t i_next = wave < nwork ? sources[source_of(wave) * parts] : 0;
   float4 e_next[DP / 4];
 #pragma unroll
   for (int q = 0; q < DP / 4; ++q)
@@ -383,7 +402,7 @@ __device__ inline void radius_unit(const RadiusArgs& A, float* lds, int ev, int 
       se[4 * q] = e_next[q].x; se[4 * q + 1] = e_next[q].y; se[4 * q + 2] = e_next[q].z; se[4 * q + 3] = e_next[q].w;
     }
     if (h + kRadiusWaves < nwork) {
-      i_next = A.bucket[a + s0 + source_of(h + kRadiusWaves)];
+      i_next = sources[source_of(h + kRadiusWaves) * parts];
 #pragma unroll
       for (int q = 0; q < DP / 4; ++q)
         e_next[q] = *reinterpret_cast<const float4*>(A.emb + (int64_t)i_next * kDpad + 4 * q);
@@ -583,11 +602,11 @@ __device__ inline void radius_unit(const RadiusArgs& A, float* lds, int ev, int 
   }
 }
 
-// One workgroup per (event, plane) unit.
-template <int MODE, int DP, bool SMALL>
-__global__ __launch_bounds__(kRadiusThreads) void k_radius(RadiusArgs A) {
+// One workgroup per (event, plane) unit and part of its sources.
+template <int MODE, int DP, int FORM>
+__global__ __launch_bounds__((RadiusShape<DP, FORM>::threads)) void k_radius(RadiusArgs A) {
   extern __shared__ float lds[];
-  radius_unit<MODE, DP, SMALL>(A, lds, blockIdx.x / A.n_planes, blockIdx.x % A.n_planes);
+  radius_unit<MODE, DP, FORM>(A, lds, blockIdx.x / A.n_planes, blockIdx.x % A.n_planes, blockIdx.y);
 }
 
 // CSR rows from the select pass's slots: thread (source i, rank r) copies
@@ -669,27 +688,44 @@ hipError_t launch_radius(const RunArgs& a, int mode, bool candidates) {
   A.slots = reinterpret_cast<int32_t*>(a.ws + a.L.slots);
   A.n_hits = a.hits.n_hits;
   A.status = a.out.status;
-  dim3 grid((unsigned)(a.hits.n_events * c.n_planes));
+  // Few units (one event: one per plane) leave the chip idle while every wave
+  // walks its sources: up to eight workgroups share a unit, each staging the
+  // window itself, as long as there are no more than two per CU (one trained
+  // full-size event 60 -> 11 us).
+  const int64_t units = a.hits.n_events * c.n_planes;
+  A.parts = (int)std::max<int64_t>(1, std::min<int64_t>(8, 2 * (int64_t)a.ctx->n_cu / units));
+  dim3 grid((unsigned)units, (unsigned)A.parts);
   const bool small = c.emb_dim <= 8;
   A.stage_window = a.ctx->radius_lds;
   A.sort_min = a.ctx->radius_sort_min;
   A.fast = a.ctx->radius_fast;
   // the split needs staged windows (it exists for the occupancy of staging)
-  A.split = a.ctx->radius_split && A.stage_window ? 1 : 0;
-#define LAUNCH_R(M_, D_, S_) \
-  hipLaunchKernelGGL((k_radius<M_, D_, S_>), grid, dim3(kRadiusThreads), (RadiusLds<D_, S_>::bytes), a.stream, A)
-#define BY_MODE(D_, S_)                                  \
-  switch (mode) {                                        \
-    case R_COUNT: LAUNCH_R(R_COUNT, D_, S_); break;      \
-    case R_EMIT: LAUNCH_R(R_EMIT, D_, S_); break;        \
-    default: LAUNCH_R(R_SELECT, D_, S_); break;          \
+  const bool split = a.ctx->radius_split && A.stage_window;
+  const bool fast = A.fast && mode == R_SELECT;
+  A.split = !split ? 0 : fast ? RadiusShape<8, R_SMALL_FAST>::cap : RadiusShape<8, R_SMALL>::cap;
+#define LAUNCH_R(M_, D_, F_)                                                                              \
+  hipLaunchKernelGGL((k_radius<M_, D_, F_>), grid, dim3(RadiusShape<D_, F_>::threads),                    \
+                     (RadiusShape<D_, F_>::bytes), a.stream, A)
+#define BY_MODE(D_)                                                  \
+  if (split && fast) LAUNCH_R(R_SELECT, D_, R_SMALL_FAST);           \
+  switch (mode) {                                                    \
+    case R_COUNT:                                                    \
+      if (split) LAUNCH_R(R_COUNT, D_, R_SMALL);                     \
+      LAUNCH_R(R_COUNT, D_, R_LARGE);                                \
+      break;                                                         \
+    case R_EMIT:                                                     \
+      if (split) LAUNCH_R(R_EMIT, D_, R_SMALL);                      \
+      LAUNCH_R(R_EMIT, D_, R_LARGE);                                 \
+      break;                                                         \
+    default:                                                         \
+      if (split && !fast) LAUNCH_R(R_SELECT, D_, R_SMALL);           \
+      LAUNCH_R(R_SELECT, D_, R_LARGE);                               \
+      break;                                                         \
   }
   if (small) {
-    if (A.split) BY_MODE(8, true)
-    BY_MODE(8, false)
+    BY_MODE(8)
   } else {
-    if (A.split) BY_MODE(16, true)
-    BY_MODE(16, false)
+    BY_MODE(16)
   }
 #undef BY_MODE
 #undef LAUNCH_R
@@ -701,19 +737,17 @@ int radius_attributes(size_t max_lds) {
   auto set = [&](const void* f) {
     bad |= hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_lds) != hipSuccess;
   };
-  for (const void* f : {reinterpret_cast<const void*>(k_radius<R_COUNT, 8, false>),
-                        reinterpret_cast<const void*>(k_radius<R_EMIT, 8, false>),
-                        reinterpret_cast<const void*>(k_radius<R_SELECT, 8, false>),
-                        reinterpret_cast<const void*>(k_radius<R_COUNT, 16, false>),
-                        reinterpret_cast<const void*>(k_radius<R_EMIT, 16, false>),
-                        reinterpret_cast<const void*>(k_radius<R_SELECT, 16, false>),
-                        reinterpret_cast<const void*>(k_radius<R_COUNT, 8, true>),
-                        reinterpret_cast<const void*>(k_radius<R_EMIT, 8, true>),
-                        reinterpret_cast<const void*>(k_radius<R_SELECT, 8, true>),
-                        reinterpret_cast<const void*>(k_radius<R_COUNT, 16, true>),
-                        reinterpret_cast<const void*>(k_radius<R_EMIT, 16, true>),
-                        reinterpret_cast<const void*>(k_radius<R_SELECT, 16, true>)})
-    set(f);
+#define SET(D_, F_)                                                  \
+  set(reinterpret_cast<const void*>(k_radius<R_COUNT, D_, F_>));     \
+  set(reinterpret_cast<const void*>(k_radius<R_EMIT, D_, F_>));      \
+  set(reinterpret_cast<const void*>(k_radius<R_SELECT, D_, F_>));
+  SET(8, R_LARGE)
+  SET(8, R_SMALL)
+  SET(16, R_LARGE)
+  SET(16, R_SMALL)
+  set(reinterpret_cast<const void*>(k_radius<R_SELECT, 8, R_SMALL_FAST>));
+  set(reinterpret_cast<const void*>(k_radius<R_SELECT, 16, R_SMALL_FAST>));
+#undef SET
   return bad;
 }
 
