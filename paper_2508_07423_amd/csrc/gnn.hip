@@ -90,6 +90,13 @@ __device__ inline int64_t logical_block(const GnnArgs& A) {
   return (b % kXcds) * (G / kXcds) + b / kXcds;
 }
 
+// A workgroup without a tile leaves before it copies its weights (the edge
+// kernels' grid does not know the number of edges: in a one-event batch most
+// workgroups have none, and their copies delayed the others').
+__device__ inline bool no_tiles(const GnnArgs& A, int64_t ntiles) {
+  return logical_block(A) * (blockDim.x >> 6) >= ntiles;
+}
+
 // Where the messages are gathered in the node kernel, the out-sums of short
 // rows are too: a node's out-edges are a few consecutive rows of the edge list,
 // which the node kernel's in-sums read anyway (as in-edges of hits one or two
@@ -650,7 +657,9 @@ __global__ __launch_bounds__(NodeThreads<P>::value) void k_node_encode(GnnArgs A
 // node encoder writes none.
 template <int H, int P, int PIPE, bool OL, bool GH>
 __global__ __launch_bounds__(512) void k_edge_encode(GnnArgs A) {
-  if (A.status[0] != 0) return;
+  const int64_t E = A.row_ptr[A.n_hits];
+  const int64_t ntiles = (E + kCols - 1) / kCols;
+  if (A.status[0] != 0 || no_tiles(A, ntiles)) return;
   extern __shared__ float lds[];
   char* w = reinterpret_cast<char*>(lds);
   stage_bytes(w, A.seg, A.seg_bytes);
@@ -662,9 +671,7 @@ __global__ __launch_bounds__(512) void k_edge_encode(GnnArgs A) {
   const int lane = lane_id(), wave = wave_id(), nw = blockDim.x >> 6;
   const float s_ee2 = asc(A, Q_EE2), o_ee2 = s_ee2 * wsc(A, SW_EE2);
   const float s_e0 = asc(A, Q_E + 0), inv_e0 = 1.0f / s_e0;
-  const int64_t E = A.row_ptr[A.n_hits];
   const bool own = kOwnForm<H, P> && own_out_sums(A, E);
-  const int64_t ntiles = (E + kCols - 1) / kCols;
   const int64_t stride = (int64_t)gridDim.x * nw;
   EdgeFeed<P, H, PIPE, GH && kHalfH<P>> feed{A.src, A.dst, nullptr, GH ? A.h : A.ps, GH ? A.h : A.pd, E, stride, lane & 15};
   feed.want_e = false;
@@ -1068,7 +1075,9 @@ __global__ __launch_bounds__(NodeThreads<P>::value) void k_node_step(GnnArgs A) 
 // when edges per node are few and the matrix cores are fast (BF16, FP8).
 template <int H, bool FINAL, int P, int PIPE, bool WR, bool OL, bool GH>
 __global__ __launch_bounds__(512) void k_edge_step(GnnArgs A) {
-  if (A.status[0] != 0) return;
+  const int64_t E = A.row_ptr[A.n_hits];
+  const int64_t ntiles = (E + kCols - 1) / kCols;
+  if (A.status[0] != 0 || no_tiles(A, ntiles)) return;
   extern __shared__ float lds[];
   char* w = reinterpret_cast<char*>(lds);
   constexpr int ES = PrecBytes<P>::value;
@@ -1086,9 +1095,7 @@ __global__ __launch_bounds__(512) void k_edge_step(GnnArgs A) {
   const int k = A.step;
   const float s_e = asc(A, Q_E + k), s_en2 = asc(A, Q_EN2), s_next = asc(A, Q_E + k + 1);
   const float w1s = wsc(A, SW_STEP + 4 * k + 2), w2s = wsc(A, SW_STEP + 4 * k + 3), wcs = wsc(A, SW_CLS1);
-  const int64_t E = A.row_ptr[A.n_hits];
   const bool own = kOwnForm<H, P> && own_out_sums(A, E);
-  const int64_t ntiles = (E + kCols - 1) / kCols;
   const int64_t stride = (int64_t)gridDim.x * nw;
   EdgeFeed<P, H, PIPE, GH && kHalfH<P>> feed{A.src, A.dst, A.e, GH ? A.h : A.ps, GH ? A.h : A.pd, E, stride, lane & 15};
   feed.want_e = true;
@@ -1233,11 +1240,21 @@ static GnnArgs gnn_args(const RunArgs& a) {
   return A;
 }
 
-static int node_threads(int prec) { return prec == P_F32 ? 1024 : 512; }
+// Threads per workgroup of the node kernels: four waves, one per SIMD, while the
+// batch has no more tiles than the chip has SIMDs (a wave then has a SIMD of its
+// own, and the weights are copied into more LDS at once).  One FP32 event of
+// 2549 hits (H = 64, 160 tiles): 30 -> 15 us per node update, with the copy of
+// tile.hpp's stage(); from 50 000 hits on large workgroups are faster, since
+// the weights are copied once per CU.
+static int node_threads(const RunArgs& a) {
+  const int64_t tiles = (a.hits.n_hits + kCols - 1) / kCols;
+  if (tiles <= 4 * (int64_t)a.ctx->n_cu) return 256;
+  return a.prec == P_F32 ? 1024 : 512;
+}
 
 static unsigned node_grid(const RunArgs& a, int per_cu) {
   int64_t tiles = (a.hits.n_hits + kCols - 1) / kCols;
-  int64_t waves = node_threads(a.prec) / 64;
+  int64_t waves = node_threads(a) / 64;
   // low-precision node kernels run two 8-wave groups per CU for each FP32 group
   if (a.prec != P_F32) per_cu *= 2;
   return (unsigned)std::max<int64_t>(1, std::min<int64_t>((tiles + waves - 1) / waves, (int64_t)a.ctx->n_cu * per_cu));
@@ -1273,9 +1290,9 @@ hipError_t launch_node_encode(const RunArgs& a) {
   A.seg_bytes = SegNodeEnc{Hh, kPrecBytes[a.prec]}.size();
   unsigned grid = node_grid(a, a.ctx->node_wg_per_cu);
   if (a.ctx->edge_products) {
-    DISPATCH_HP(Hh, a.prec, hipLaunchKernelGGL((k_node_encode<H, P, false>), dim3(grid), dim3(node_threads(P)), A.seg_bytes, a.stream, A));
+    DISPATCH_HP(Hh, a.prec, hipLaunchKernelGGL((k_node_encode<H, P, false>), dim3(grid), dim3(node_threads(a)), A.seg_bytes, a.stream, A));
   } else {
-    DISPATCH_HP(Hh, a.prec, hipLaunchKernelGGL((k_node_encode<H, P, true>), dim3(grid), dim3(node_threads(P)), A.seg_bytes, a.stream, A));
+    DISPATCH_HP(Hh, a.prec, hipLaunchKernelGGL((k_node_encode<H, P, true>), dim3(grid), dim3(node_threads(a)), A.seg_bytes, a.stream, A));
   }
   return hipGetLastError();
 }
@@ -1415,7 +1432,7 @@ hipError_t launch_node_step(const RunArgs& a, int k) {
   unsigned grid = node_grid(a, a.ctx->node_wg_per_cu);
   const bool np = !a.ctx->edge_products;
 #define NODE_K(F_, N_) \
-  DISPATCH_HP(Hh, a.prec, hipLaunchKernelGGL((k_node_step<H, P, F_, N_>), dim3(grid), dim3(node_threads(P)), A.seg_bytes, a.stream, A))
+  DISPATCH_HP(Hh, a.prec, hipLaunchKernelGGL((k_node_step<H, P, F_, N_>), dim3(grid), dim3(node_threads(a)), A.seg_bytes, a.stream, A))
   if (a.ctx->fuse_messages && np) {
     NODE_K(true, true);
   } else if (a.ctx->fuse_messages) {

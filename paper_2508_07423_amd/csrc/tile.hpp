@@ -491,10 +491,22 @@ __device__ inline void ln_relu(float* a) {
   for (int r = 0; r < F / 4; ++r) a[r] = fmaxf((a[r] - mean) * rstd, 0.f);
 }
 
-// Copy n floats global -> LDS with 16-byte accesses (n multiple of 4, both aligned).
+// Copy n floats global -> LDS with 16-byte accesses (n multiple of 4, both
+// aligned).  Eight loads per thread are in flight: a small batch's kernels are
+// as long as this copy's round trips to memory (98 KB of node weights, 256
+// threads: three instead of twenty-four).  The eight are not conditional: with
+// a test per load the kernels that copy less took up to twice as long.
 __device__ inline void stage(float* __restrict__ dst, const float* __restrict__ src, int n) {
-  for (int i = threadIdx.x * 4; i < n; i += blockDim.x * 4)
-    *reinterpret_cast<float4*>(dst + i) = *reinterpret_cast<const float4*>(src + i);
+  const int step = blockDim.x * 4;
+  int i = threadIdx.x * 4;
+  for (; i + 7 * step < n; i += 8 * step) {
+    float4 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const float4*>(src + i + u * step);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) *reinterpret_cast<float4*>(dst + i + u * step) = v[u];
+  }
+  for (; i < n; i += step) *reinterpret_cast<float4*>(dst + i) = *reinterpret_cast<const float4*>(src + i);
 }
 
 }  // namespace etx
