@@ -1063,6 +1063,77 @@ __global__ __launch_bounds__(NodeThreads<P>::value) void k_node_step(GnnArgs A) 
   }
 }
 
+// The FP32 node update of a small batch.  A workgroup is one tile of 16 nodes,
+// each wave forms one block of 16 features: the large form has a whole tile's 384
+// MFMAs, 5 us at H = 64, in one wave, and copies all weights to LDS first.  Here a
+// wave loads its part of the weights into registers at once, and the waves
+// exchange the blocks through LDS, so that every wave normalises whole columns.
+// Every sum has the terms of k_node_step in the same order.
+template <int H, bool NP>
+__global__ __launch_bounds__(4 * H) void k_node_step_small(GnnArgs A) {
+  if (A.status[0] != 0) return;
+  constexpr int LS = H + 4;                  // floats per column in LDS
+  __shared__ __align__(16) float buf[2][kCols * LS];
+  constexpr SegNode S{H, 4};
+  const int lane = lane_id(), g = lane_group(), mb = wave_id();
+  const int f = 16 * mb + 4 * g;             // this lane's four features of column col
+  const int64_t col = (int64_t)blockIdx.x * kCols + (lane & 15);
+  const bool valid = col < A.n_hits;
+  float x[3 * H / 4];
+  load_h<H, P_F32>(x, A, col, valid);
+  float w1[3 * H / 4], w2[H / 4], ws[H / 4], wd[H / 4], a[H / 4], o[H / 4];
+  const float* seg = reinterpret_cast<const float*>(A.seg);
+  load_wreg<3 * H, 1>(w1, seg + S.w1() / 4 + mb * (3 * H / 4) * 64);
+  load_wreg<H, 1>(w2, seg + S.w2() / 4 + mb * (H / 4) * 64);
+  if constexpr (NP) {
+    load_wreg<H, 1>(ws, seg + S.ws() / 4 + mb * (H / 4) * 64);
+    load_wreg<H, 1>(wd, seg + S.wd() / 4 + mb * (H / 4) * 64);
+  }
+  const float4 b1 = *reinterpret_cast<const float4*>(seg + S.b1() / 4 + f);
+  const float4 b2 = *reinterpret_cast<const float4*>(seg + S.b2() / 4 + f);
+  load_cols<H>(x + H / 4, A.msg + col * 2 * H, valid);
+  load_cols<H>(x + H / 2, A.msg + col * 2 * H + H, valid);
+  // a block of 16 features per wave -> whole columns in every wave
+  const int at = (lane & 15) * LS;
+  auto put = [&](int b, const float4& v) { *reinterpret_cast<float4*>(&buf[b][at + f]) = v; };
+  auto get = [&](int b, float* r) {
+#pragma unroll
+    for (int c = 0; c < H / 16; ++c) {
+      const float4 v = *reinterpret_cast<const float4*>(&buf[b][at + 16 * c + 4 * g]);
+      r[4 * c] = v.x;
+      r[4 * c + 1] = v.y;
+      r[4 * c + 2] = v.z;
+      r[4 * c + 3] = v.w;
+    }
+  };
+  float q[4] = {b1.x, b1.y, b1.z, b1.w};
+  mfma_f32_reg<3 * H, 1>(q, x, w1);
+  put(0, make_float4(q[0], q[1], q[2], q[3]));
+  __syncthreads();
+  get(0, a);
+  ln_relu<H>(a);
+  q[0] = b2.x, q[1] = b2.y, q[2] = b2.z, q[3] = b2.w;
+  mfma_f32_reg<H, 1>(q, a, w2);
+  put(1, make_float4(q[0], q[1], q[2], q[3]));
+  __syncthreads();
+  get(1, o);
+  ln_relu<H>(o);
+#pragma unroll
+  for (int r = 0; r < H / 4; ++r) o[r] += x[r];
+#pragma unroll
+  for (int c = 0; c < H / 16; ++c)           // c == mb, without indexing registers by a variable
+    if (c == mb && valid)
+      *reinterpret_cast<float4*>(A.h + col * H + f) = make_float4(o[4 * c], o[4 * c + 1], o[4 * c + 2], o[4 * c + 3]);
+  if constexpr (NP) {
+    q[0] = q[1] = q[2] = q[3] = 0.f;
+    mfma_f32_reg<H, 1>(q, o, ws);
+    if (valid) *reinterpret_cast<float4*>(A.ps + col * H + f) = make_float4(q[0], q[1], q[2], q[3]);
+    q[0] = q[1] = q[2] = q[3] = 0.f;
+    mfma_f32_reg<H, 1>(q, o, wd);
+    if (valid) *reinterpret_cast<float4*>(A.pd + col * H + f) = make_float4(q[0], q[1], q[2], q[3]);
+  }
+}
+
 // --------------------------------------------------------------------------
 // edge update k; the last step also runs the classifier and writes scores
 // --------------------------------------------------------------------------
@@ -1252,6 +1323,17 @@ static int node_threads(const RunArgs& a) {
   return a.prec == P_F32 ? 1024 : 512;
 }
 
+// The one-tile form of the node update (k_node_step_small): FP32, while the chip
+// has room for all its waves at once.  Beyond that the copies of the weights,
+// 98 KB per tile at H = 64, cost more than the shorter chain saves: one, two, six
+// full-size events (H = 64, 160, 320, 965 tiles) 9.0 -> 4.5, 10.2 -> 8.1 and 12.4
+// -> 15.9 us, H = 32 at 30, 340 and 1280 tiles 3.4 -> 2.0, 5.2 -> 3.5 and 9.3 ->
+// 6.0 us.  Calibration runs keep the large form, which observes its values.
+static bool node_small(const RunArgs& a) {
+  const int64_t tiles = (a.hits.n_hits + kCols - 1) / kCols;
+  return a.prec == P_F32 && !a.calibrate && !a.ctx->fuse_messages && tiles <= (a.ctx->cfg.gnn_hidden == 64 ? 2 : 8) * (int64_t)a.ctx->n_cu;
+}
+
 static unsigned node_grid(const RunArgs& a, int per_cu) {
   int64_t tiles = (a.hits.n_hits + kCols - 1) / kCols;
   int64_t waves = node_threads(a) / 64;
@@ -1407,7 +1489,11 @@ hipError_t launch_segsum(const RunArgs& a, int k) {
   A.step = k;
   const int Hh = a.ctx->cfg.gnn_hidden;
   unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((a.hits.n_hits + 3) / 4, (int64_t)a.ctx->n_cu * 32));
-  const int U = a.ctx->segsum_unroll;
+  // A small batch leaves a SIMD too few waves to hide the chain of a node's rows: eight
+  // are in flight (four before; one event of 481 hits 6.7 -> 5.2 us, one dense full-size
+  // event 18 -> 14, three 25 -> 22, eight no gain; sixteen cost sparse events 0.6 us).
+  constexpr int64_t kSmallHits = 16384;
+  const int U = a.hits.n_hits <= kSmallHits ? 8 : a.ctx->segsum_unroll;
   // the sums read the stored edge rows: FP32 whenever the state is kept in FP32
   const int sp = (a.prec == P_BF16 || a.prec == P_FP8) ? a.prec : P_F32;
 #define SEG_U(U_) DISPATCH_HP(Hh, sp, hipLaunchKernelGGL((k_segsum<H, P, U_>), dim3(grid), dim3(256), 0, a.stream, A))
@@ -1431,6 +1517,16 @@ hipError_t launch_node_step(const RunArgs& a, int k) {
   A.step = k;
   unsigned grid = node_grid(a, a.ctx->node_wg_per_cu);
   const bool np = !a.ctx->edge_products;
+  if (node_small(a)) {
+    const dim3 tiles((unsigned)((a.hits.n_hits + kCols - 1) / kCols));
+#define NODE_S(H_, N_) hipLaunchKernelGGL((k_node_step_small<H_, N_>), tiles, dim3(4 * H_), 0, a.stream, A)
+    if (Hh == 32 && np) NODE_S(32, true);
+    else if (Hh == 32) NODE_S(32, false);
+    else if (np) NODE_S(64, true);
+    else NODE_S(64, false);
+#undef NODE_S
+    return hipGetLastError();
+  }
 #define NODE_K(F_, N_) \
   DISPATCH_HP(Hh, a.prec, hipLaunchKernelGGL((k_node_step<H, P, F_, N_>), dim3(grid), dim3(node_threads(a)), A.seg_bytes, a.stream, A))
   if (a.ctx->fuse_messages && np) {

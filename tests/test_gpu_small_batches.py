@@ -1,5 +1,5 @@
-"""An event alone (node kernels of four waves, edge workgroups without a tile
-leave at once) and inside a batch large enough for the full workgroups: the same
+"""An event alone (node update with one workgroup per 16 nodes or with workgroups
+of four waves, edge workgroups without a tile leave at once) and inside a batch large enough for the full workgroups: the same
 edges, scores and labels, bit for bit."""
 import numpy as np
 import pytest
@@ -12,7 +12,9 @@ torch = pytest.importorskip("torch")
 
 @pytest.mark.parametrize("precision", ["ETX_FP32", "ETX_BF16", "ETX_FP8_E4M3"])
 @pytest.mark.parametrize("name,tracks,products,fuse,compact", [("c1", 3, 1, 0, 0), ("c1", 60, 0, 0, 1), ("c2", 5, 1, 0, 1),
-                                                               ("c2", 130, 0, 1, 1), ("c2", 257, 1, 1, 0), ("c3", 64, 1, 1, 1)])
+                                                               ("c2", 130, 0, 1, 1), ("c2", 257, 1, 1, 0), ("c3", 64, 1, 1, 1),
+                                                               ("c2", 130, 0, 0, 0), ("c2", 600, 0, 0, 0), ("c2", 900, 1, 0, 0),
+                                                               ("c3", 257, 0, 0, 1)])
 def test_event_alone_and_in_a_batch(name, tracks, products, fuse, compact, precision):
     from paper_2508_07423_amd import etx
     w = synth.WORKLOADS[name].with_(gnn_steps=3, tracks=("fixed", tracks))
