@@ -38,7 +38,8 @@ struct RadiusArgs {
   int stage_window;        // 0: always read the window from HBM
   int sort_min;            // staged windows of at least this many hits are sorted (cell list)
   int fast;                // select pass: sources with at most kFastList in-radius candidates take the fast path
-  int parts;               // workgroups that share a unit's sources (blockIdx.y takes every parts-th)
+  int parts;               // workgroups that may share a unit's sources (blockIdx.y takes every parts-th)
+  int part_sources;        // sources per workgroup that shares
   int split;               // > 0: windows of up to this many hits go to the small workgroups' launch, the rest to the other
   float r2, r;
   int32_t* cnt;            // count pass output (and the select pass's)
@@ -150,8 +151,9 @@ __device__ inline void radius_unit(const RadiusArgs& A, float* lds, int ev, int 
   const int nwin = window_hits(po, p, P, A.window);
   if (status != 0) return;
   // this workgroup's sources: number part, part + parts, ... of the unit
-  const int parts = A.parts, nsrc = (s1 - s0 - part + parts - 1) / parts;
-  if (nsrc <= 0) return;
+  const int parts = min(A.parts, (s1 - s0 + A.part_sources - 1) / A.part_sources);
+  if (part >= parts) return;
+  const int nsrc = (s1 - s0 - part + parts - 1) / parts;
   const int32_t* sources = A.bucket + a + s0 + part;
   const int w0 = s1;
   // split launches: each unit goes to exactly one of the two
@@ -611,20 +613,20 @@ __global__ __launch_bounds__((RadiusShape<DP, FORM>::threads)) void k_radius(Rad
 
 // CSR rows from the select pass's slots: thread (source i, rank r) copies
 // slot r of source i when r is below its count.
-// One wave per chunk of 64 hits.  The chunk's CSR rows are one contiguous
-// range of the output, so lane l writes positions l, l + 64, ... of it (every
-// store coalesced, no idle lanes whatever the row lengths); the row of a
-// position is found by a binary search over the chunk's row starts, one per
-// lane, read with lane shuffles.
+// One wave (few hits: `parts` waves, taking rounds in turn) per chunk of 64 hits.
+// The chunk's CSR rows are one contiguous range of the output, so lane l writes
+// positions l, l + 64, ... of it (every store coalesced, no idle lanes whatever
+// the row lengths); the row of a position is found by a binary search over the
+// chunk's row starts, one per lane, read with lane shuffles.
 __global__ __launch_bounds__(256) void k_slots_to_csr(const int32_t* __restrict__ slots, const int64_t* __restrict__ row_ptr,
-                                                      int64_t n_hits, int k_max, int32_t* __restrict__ src,
+                                                      int64_t n_hits, int k_max, int parts, int32_t* __restrict__ src,
                                                       int32_t* __restrict__ dst, const int64_t* status) {
   if (status[0] != 0) return;
   const int lane = threadIdx.x & 63;
   const int64_t nchunks = (n_hits + 63) / 64;
   const int64_t stride = (int64_t)gridDim.x * (blockDim.x / 64);
-  for (int64_t ch = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / 64; ch < nchunks; ch += stride) {
-    const int64_t h0 = ch * 64;
+  for (int64_t w = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / 64; w < nchunks * parts; w += stride) {
+    const int64_t h0 = w / parts * 64;
     const int64_t base = row_ptr[h0];
     const int64_t end = row_ptr[min(h0 + 64, n_hits)];
     // row start of this lane's hit relative to the chunk (past the last hit:
@@ -632,7 +634,7 @@ __global__ __launch_bounds__(256) void k_slots_to_csr(const int32_t* __restrict_
     const int rel = (int)((h0 + lane < n_hits ? row_ptr[h0 + lane] : end) - base);
     const int total = (int)(end - base);
     // the whole wave runs every round (the shuffles read every lane's rel)
-    for (int q0 = 0; q0 < total; q0 += 64) {
+    for (int q0 = (int)(w % parts) * 64; q0 < total; q0 += 64 * parts) {
       const int q = q0 + lane;
       int lo = 0, hi = 63;                       // largest l with rel_l <= q
 #pragma unroll
@@ -657,12 +659,15 @@ hipError_t launch_slots_copy(const RunArgs& a, bool candidates) {
   if (n == 0) return hipSuccess;
   const int k = a.ctx->cfg.k_max;
   const int64_t chunks = (n + 63) / 64;
-  const unsigned grid = (unsigned)std::min<int64_t>((chunks + 3) / 4, (int64_t)a.ctx->n_cu * 32);
+  // few chunks leave the chip idle while a wave walks its rows: up to sixteen waves
+  // share one (481 hits of 11 edges each 16 -> 4 us)
+  const int parts = (int)std::max<int64_t>(1, std::min<int64_t>(16, 4 * (int64_t)a.ctx->n_cu / chunks));
+  const unsigned grid = (unsigned)std::min<int64_t>((chunks * parts + 3) / 4, (int64_t)a.ctx->n_cu * 32);
   const int32_t* slots = reinterpret_cast<const int32_t*>(a.ws + a.L.slots);
   const int64_t* rp = reinterpret_cast<const int64_t*>(a.ws + (candidates ? a.L.pf_tmp : a.L.row_ptr));
   int32_t* s = candidates ? reinterpret_cast<int32_t*>(a.ws + a.L.cand_src) : a.out.src;
   int32_t* d = candidates ? reinterpret_cast<int32_t*>(a.ws + a.L.cand_dst) : a.out.dst;
-  hipLaunchKernelGGL(k_slots_to_csr, dim3(grid), dim3(256), 0, a.stream, slots, rp, n, k, s, d, a.out.status);
+  hipLaunchKernelGGL(k_slots_to_csr, dim3(grid), dim3(256), 0, a.stream, slots, rp, n, k, parts, s, d, a.out.status);
   return hipGetLastError();
 }
 
@@ -689,11 +694,16 @@ hipError_t launch_radius(const RunArgs& a, int mode, bool candidates) {
   A.n_hits = a.hits.n_hits;
   A.status = a.out.status;
   // Few units (one event: one per plane) leave the chip idle while every wave
-  // walks its sources: up to eight workgroups share a unit, each staging the
-  // window itself, as long as there are no more than two per CU (one trained
-  // full-size event 60 -> 11 us).
+  // walks its sources, and the largest unit of an uneven batch outlasts the
+  // others: up to eight workgroups share a unit, each staging the window itself.
+  // The more units, the more sources each must have to pay for that.  One trained
+  // full-size event 60 -> 11 us; 20 and 100 uneven events of a trained network (two
+  // and one workgroup per unit -> shared) 98 -> 48 and 176 -> 147 us, of a dense one
+  // 298 -> 117 and 654 -> 476 us; 400 (12,000 units) gain if dense (1.77 -> 1.51 ms)
+  // and lose if sparse (0.53 -> 0.55 ms).
   const int64_t units = a.hits.n_events * c.n_planes;
-  A.parts = (int)std::max<int64_t>(1, std::min<int64_t>(8, 2 * (int64_t)a.ctx->n_cu / units));
+  A.parts = units <= 32 * (int64_t)a.ctx->n_cu ? 8 : 1;
+  A.part_sources = (int)std::max<int64_t>(1, std::min<int64_t>(128, units / 8));
   dim3 grid((unsigned)units, (unsigned)A.parts);
   const bool small = c.emb_dim <= 8;
   A.stage_window = a.ctx->radius_lds;
