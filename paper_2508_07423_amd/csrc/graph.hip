@@ -198,12 +198,11 @@ __global__ __launch_bounds__(256) void k_scan_top(int64_t* __restrict__ part, in
 
 // Row offsets of the kScanBlock counts from i0 on, eight consecutive counts per
 // thread of a 1024-thread workgroup, starting at `carry`, which moves past them.
-// One barrier: `tot` holds two slots that alternate between calls.
 constexpr int kScanThreads = 1024;
 static_assert(kScanBlock == 8 * kScanThreads, "eight counts per thread");
 
 __device__ inline void scan_counts(const int32_t* __restrict__ cnt, int64_t i0, int64_t n, int64_t* __restrict__ row_ptr,
-                                   int64_t& carry, int (&tot)[2][kScanThreads / 64], int slot) {
+                                   int64_t& carry, int (&tot)[kScanThreads / 64]) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int64_t i = i0 + (int64_t)t * 8;
   int v[8] = {};
@@ -219,9 +218,9 @@ __device__ inline void scan_counts(const int32_t* __restrict__ cnt, int64_t i0, 
 #pragma unroll
   for (int u = 0; u < 8; ++u) sum += v[u];
   const int inc = wave_inclusive_scan(sum);
-  if (lane == 63) tot[slot][wave] = inc;
+  if (lane == 63) tot[wave] = inc;
   __syncthreads();
-  const int of_wave = lane < kScanThreads / 64 ? tot[slot][lane] : 0;
+  const int of_wave = lane < kScanThreads / 64 ? tot[lane] : 0;
   const int waves = wave_inclusive_scan(of_wave);
   int64_t at = carry + __shfl(waves - of_wave, wave) + inc - sum;
   carry += __shfl(waves, kScanThreads / 64 - 1);
@@ -247,34 +246,83 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down(const int32_t* __res
                                                             const int64_t* __restrict__ part,
                                                             int64_t* __restrict__ row_ptr, const int64_t* status) {
   if (status[0] != 0) return;
-  __shared__ int tot[2][kScanThreads / 64];
+  __shared__ int tot[kScanThreads / 64];
   int64_t base = part[blockIdx.x];
-  scan_counts(cnt, (int64_t)blockIdx.x * kScanBlock, n, row_ptr, base, tot, 0);
+  scan_counts(cnt, (int64_t)blockIdx.x * kScanBlock, n, row_ptr, base, tot);
 }
 
-// The whole scan of a small batch in one workgroup, with the capacity check and
-// the per-event edge offsets: three launches fewer.  Up to kSmallScan counts
-// (two blocks) that is the shorter way; what a small batch pays is latency (one
-// event 25 -> 6 us).
-constexpr int64_t kSmallScan = 2 * kScanBlock;
+// The whole scan of a small batch in one launch, with the capacity check and the
+// per-event edge offsets: three launches fewer.  Every workgroup adds up all
+// counts, for its own start and for the check, and scans its own block; what a
+// small batch pays is latency: one event 25 -> 6 us, 39,000 hits (five blocks) 17 ->
+// 8, 78,000 17 -> 12; 180,000 hits take 17 in four launches and 21 in one.
+constexpr int64_t kSmallScan = 16 * kScanBlock;
 
 __global__ __launch_bounds__(kScanThreads) void k_scan_small(const int32_t* __restrict__ cnt, int64_t n,
                                                              int64_t* __restrict__ row_ptr, int64_t capacity,
                                                              const int64_t* __restrict__ hit_off, int64_t n_events,
                                                              int64_t* __restrict__ edge_off, int64_t* status) {
-  __shared__ int tot[2][kScanThreads / 64];
+  __shared__ int tot[kScanThreads / 64];
+  __shared__ int64_t sums[2][kScanThreads / 64];
   __shared__ int64_t bad;
   if (status[0] != 0) return;
-  int64_t carry = 0;
-  int slot = 0;
-  for (int64_t i0 = 0; i0 < n; i0 += kScanBlock, slot ^= 1) scan_counts(cnt, i0, n, row_ptr, carry, tot, slot);
-  if (threadIdx.x == 0) {
-    row_ptr[n] = carry;
-    bad = check_edges(carry, capacity, status);
+  const int t = threadIdx.x, lane = t & 63;
+  const int64_t i0 = (int64_t)blockIdx.x * kScanBlock, i1 = i0 + kScanBlock;
+  const bool last = blockIdx.x + 1 == gridDim.x;
+  int64_t before = 0, all = 0;
+  if (gridDim.x > 1) {
+    constexpr int kBatch = 4;
+    for (int64_t q0 = (int64_t)t * 4; q0 < n; q0 += 4 * kScanThreads * kBatch) {
+      int4 v[kBatch];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
+        const int64_t q = q0 + u * 4 * kScanThreads;
+        v[u] = make_int4(0, 0, 0, 0);
+        if (q + 4 <= n) v[u] = *reinterpret_cast<const int4*>(cnt + q);
+        else if (q < n) v[u] = make_int4(cnt[q], q + 1 < n ? cnt[q + 1] : 0, q + 2 < n ? cnt[q + 2] : 0, 0);
+      }
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
+        const int64_t s = (int64_t)v[u].x + v[u].y + v[u].z + v[u].w;
+        all += s;
+        if (q0 + u * 4 * kScanThreads < i0) before += s;
+      }
+    }
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) {
+      all += __shfl_xor(all, m);
+      before += __shfl_xor(before, m);
+    }
+    if (lane == 0) {
+      sums[0][t >> 6] = before;
+      sums[1][t >> 6] = all;
+    }
+    __syncthreads();
+    before = all = 0;
+#pragma unroll
+    for (int w = 0; w < kScanThreads / 64; ++w) {
+      before += sums[0][w];
+      all += sums[1][w];
+    }
+  }
+  // more edges than fit: only the last workgroup reports it, none writes offsets
+  const bool fits = gridDim.x == 1 || (all <= capacity && all < 0x7fffffffLL);
+  int64_t carry = before;
+  if (fits) scan_counts(cnt, i0, n, row_ptr, carry, tot);
+  if (t == 0) {
+    bad = !fits;
+    if (gridDim.x == 1) all = carry;
+    if (last) {
+      row_ptr[n] = all;
+      bad = check_edges(all, capacity, status);
+    }
   }
   __syncthreads();
   if (!edge_off || bad) return;
-  for (int64_t e = threadIdx.x; e <= n_events; e += kScanThreads) edge_off[e] = row_ptr[hit_off[e]];
+  for (int64_t e = t; e <= n_events; e += kScanThreads) {
+    const int64_t h = hit_off[e];
+    if (h >= i0 && (h < i1 || last)) edge_off[e] = row_ptr[h];
+  }
 }
 
 __global__ void k_edge_off(const int64_t* __restrict__ hit_off, int64_t n_events, const int64_t* __restrict__ row_ptr,
@@ -721,7 +769,7 @@ hipError_t launch_scan_counts(const RunArgs& a, bool candidates) {
   int64_t* part = WS(a, scan_tmp, int64_t);
   int64_t* row_ptr = candidates ? WS(a, pf_tmp, int64_t) : WS(a, row_ptr, int64_t);
   if (n <= kSmallScan) {
-    hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(kScanThreads), 0, a.stream, WS(a, cnt, int32_t), n, row_ptr,
+    hipLaunchKernelGGL(k_scan_small, dim3((unsigned)std::max<int64_t>(1, nb)), dim3(kScanThreads), 0, a.stream, WS(a, cnt, int32_t), n, row_ptr,
                        a.out.edge_capacity, a.hits.hit_off, a.hits.n_events, candidates ? nullptr : a.out.edge_off,
                        a.out.status);
     return hipGetLastError();

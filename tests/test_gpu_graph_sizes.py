@@ -1,7 +1,7 @@
 """Plane bucketing, row offsets and the (dst, src) permutation at the event and
 batch sizes where their kernels change form: the small and the wide CSC
 workgroups (4,096 hits, one event per CU), row ranges of the largest event,
-placement over several column ranges, one and two scan blocks and more,
+placement over several column ranges, one to seventeen scan blocks,
 shuffled hits.  All are whole numbers with one right answer, formed with numpy
 from the run's own edges."""
 import numpy as np
@@ -38,7 +38,7 @@ MANY = [17 + (i * 37) % 90 for i in range(300)]
 @pytest.mark.parametrize("sizes,k_max,least", [
     ([1], 32, 0), ([0, 63, 0, 64, 65, 0], 32, 0), ([4096], 6, 2), ([4097, 5], 6, 2), ([4096, 4097], 32, 16),
     ([8192], 6, 2), ([8193], 32, 16), ([16384], 32, 16), ([16384], 6, 2), ([8192, 8193], 32, 16), (MANY, 32, 0),
-    (MANY + [4097, 0, 4500], 6, 2)])
+    (MANY + [4097, 0, 4500], 6, 2), ([16384, 16384, 1], 6, 2), ([16384] * 8, 6, 2), ([16384] * 8 + [3, 0], 6, 2)])
 def test_graph_kernels_at_sizes(sizes, k_max, least, place):
     from paper_2508_07423_amd import etx
     w = synth.C1.with_(k_max=k_max)
@@ -94,3 +94,22 @@ def test_components_at_sizes(sizes, kept):
     share = keep.mean()
     assert share == 1 if kept == "all" else 0.1 < share < 0.3
     assert np.array_equal(res["labels"], O.components(b.n_hits, res["src"], res["dst"], keep))
+
+
+@pytest.mark.parametrize("sizes", [[300], [8192, 1], [9000, 9000, 0], [16384] * 8, [16384] * 8 + [1]])
+def test_too_many_edges_at_sizes(sizes):
+    """One edge more than fits is reported with the need, whichever form the scan has; the need itself fits."""
+    from paper_2508_07423_amd import etx
+    w = synth.C1.with_(k_max=6, gnn_steps=1)
+    b = etx.to_device(_batch(sizes))
+    p = etx.Pipeline(w, synth.xavier_weights(w))
+    p.run(b)
+    need = len(p.results(b)["src"])
+    assert need > 0
+    p.run(b, need - 1)
+    torch.cuda.synchronize()
+    st = p.status.cpu().numpy()
+    assert st[0] == etx.ETX_ERR_CAPACITY and st[1] == need
+    p.run(b, need)
+    assert len(p.results(b)["src"]) == need
+    p.close()
