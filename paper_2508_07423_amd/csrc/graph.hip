@@ -436,13 +436,23 @@ __global__ __launch_bounds__(256) void k_csc_place(const int64_t* __restrict__ h
 constexpr int kCscThreads = 1024, kCscWaves = kCscThreads / 64;
 constexpr int kCscWords = 32768;                  // 128 KiB: two cursors per hit of the largest event
 static_assert(kCscWords >= 2 * ETX_MAX_EVENT_HITS, "two ranges of the largest event");
+// Batches of small events take half: as many ranges for an event of up to 1,024
+// hits, one of the largest (an event of over 8,192 walks).  Their workgroups, most
+// of them without work, need not wait for a CU whose whole LDS is free behind the
+// kernels of a batch on another stream (6,489 events of a trained network, two
+// batches in turn 7.32 -> 7.02 ms each).
+constexpr int kCscFewWords = 16384;
+constexpr int kCscFewHits = 1024;                 // hits per event on average
+static_assert(kCscFewWords >= ETX_MAX_EVENT_HITS, "one range of the largest event");
+static_assert(kCscFewWords >= kCscWaves * kCscFewHits, "every wave a range");
 
 // place: short rows may be placed; every_event: the place kernel is not launched
 __global__ __launch_bounds__(kCscThreads) void k_csc_wide(const int64_t* __restrict__ hit_off,
                                                           const int64_t* __restrict__ row_ptr,
                                                           const int32_t* __restrict__ dst,
                                                           int64_t* __restrict__ col_ptr, int32_t* __restrict__ csc,
-                                                          int place, int every_event, const int64_t* status) {
+                                                          int place, int every_event, int words,
+                                                          const int64_t* status) {
   extern __shared__ int cur[];                    // [ranges][n] cursors, or n cursors and the placed edges
   __shared__ int tot[2][kCscWaves];
   if (status[0] != 0) return;
@@ -457,8 +467,9 @@ __global__ __launch_bounds__(kCscThreads) void k_csc_wide(const int64_t* __restr
     if (t == 0) col_ptr[a] = ee;
     return;
   }
-  const bool placed = place && edges < (int64_t)kCscRowWalk * n;
-  const int R = placed ? 1 : min(kCscWaves, kCscWords / n);
+  // a column may hold n edges, which have to fit beside the n cursors
+  const bool placed = place && edges < (int64_t)kCscRowWalk * n && 2 * n <= words;
+  const int R = placed ? 1 : min(kCscWaves, words / n);
   const int per = (n + R - 1) / R;                // rows per range
   for (int i = t; i < R * n; i += kCscThreads) cur[i] = 0;
   __syncthreads();
@@ -510,7 +521,7 @@ __global__ __launch_bounds__(kCscThreads) void k_csc_wide(const int64_t* __restr
     // cursor i is the start of column i until its edges are placed, its end
     // afterwards; as many columns at a time as their edges fit beside the cursors
     int* list = cur + n;
-    const int room = kCscWords - n;
+    const int room = words - n;
     for (int lo = 0; lo < n;) {
       const int begin = cur[lo];
       int hi = n;
@@ -798,9 +809,11 @@ hipError_t launch_csc(const RunArgs& a) {
   if (!wide_only)
     hipLaunchKernelGGL(k_csc_place, grid, dim3(256), 0, a.stream, a.hits.hit_off, WS(a, row_ptr, int64_t), a.out.dst,
                        WS(a, col_ptr, int64_t), WS(a, csc, int32_t), a.out.status);
-  hipLaunchKernelGGL(k_csc_wide, grid, dim3(kCscThreads), sizeof(int) * kCscWords, a.stream, a.hits.hit_off,
+  const bool few_hits = !wide_only && a.hits.n_hits <= kCscFewHits * a.hits.n_events;
+  const int words = few_hits ? kCscFewWords : kCscWords;
+  hipLaunchKernelGGL(k_csc_wide, grid, dim3(kCscThreads), sizeof(int) * words, a.stream, a.hits.hit_off,
                      WS(a, row_ptr, int64_t), a.out.dst, WS(a, col_ptr, int64_t), WS(a, csc, int32_t), place,
-                     wide_only ? 1 : 0, a.out.status);
+                     wide_only ? 1 : 0, words, a.out.status);
   return hipGetLastError();
 }
 

@@ -38,7 +38,8 @@ MANY = [17 + (i * 37) % 90 for i in range(300)]
 @pytest.mark.parametrize("sizes,k_max,least", [
     ([1], 32, 0), ([0, 63, 0, 64, 65, 0], 32, 0), ([4096], 6, 2), ([4097, 5], 6, 2), ([4096, 4097], 32, 16),
     ([8192], 6, 2), ([8193], 32, 16), ([16384], 32, 16), ([16384], 6, 2), ([8192, 8193], 32, 16), (MANY, 32, 0),
-    (MANY + [4097, 0, 4500], 6, 2), ([16384, 16384, 1], 6, 2), ([16384] * 8, 6, 2), ([16384] * 8 + [3, 0], 6, 2)])
+    (MANY + [4097, 0, 4500], 6, 2), ([16384, 16384, 1], 6, 2), ([16384] * 8, 6, 2), ([16384] * 8 + [3, 0], 6, 2),
+    (MANY + [8192, 8193], 6, 2), (MANY + [16384], 6, 2), (MANY + [16384, 4097], 32, 16)])
 def test_graph_kernels_at_sizes(sizes, k_max, least, place):
     from paper_2508_07423_amd import etx
     w = synth.C1.with_(k_max=k_max)
