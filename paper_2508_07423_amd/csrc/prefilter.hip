@@ -330,27 +330,33 @@ __global__ void k_pf_reduce_chunks(float* __restrict__ partial, int n_waves, con
   partial[(int64_t)w0 * kPfGradStride + i] = s;
 }
 
-__global__ void k_pf_reduce(const float* __restrict__ partial, int n_waves, float* __restrict__ grad, float* loss,
-                            const int64_t* status) {
+// The chunk sums are added in chunk order, sixteen loads in flight, and the
+// parameter is updated (20 events: the step 133 -> 120 us, the two
+// launches this replaces 14.6 + 4.8 us).
+__global__ __launch_bounds__(64) void k_pf_update(const float* __restrict__ partial, int n_waves, float* __restrict__ grad,
+                                                  float* loss, float* __restrict__ p, float* __restrict__ m,
+                                                  float* __restrict__ v, float lr, float b1, float b2, float eps,
+                                                  float c1, float c2, const int64_t* status) {
   if (status[0] != 0) return;
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i > N_P) return;
   const int per = (n_waves + kPfChunks - 1) / kPfChunks;
+  constexpr int kBatch = 16;
   float s = 0.f;
-  for (int w0 = 0; w0 < n_waves; w0 += per) s += partial[(int64_t)w0 * kPfGradStride + i];
+  for (int w0 = 0; w0 < n_waves; w0 += kBatch * per) {
+    float x[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) x[u] = w0 + u * per < n_waves ? partial[(int64_t)(w0 + u * per) * kPfGradStride + i] : 0.f;
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) s += x[u];
+  }
   grad[i] = s;
-  if (i == N_P && loss) *loss = s;
-}
-
-__global__ void k_pf_adam(float* __restrict__ p, float* __restrict__ m, float* __restrict__ v,
-                          const float* __restrict__ grad, float lr, float b1, float b2, float eps, float c1, float c2,
-                          const int64_t* status) {
-  if (status[0] != 0) return;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= N_P) return;
-  const float gi = grad[i];
-  const float mi = b1 * m[i] + (1.f - b1) * gi;
-  const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
+  if (i == N_P) {
+    if (loss) *loss = s;
+    return;
+  }
+  const float mi = b1 * m[i] + (1.f - b1) * s;
+  const float vi = b2 * v[i] + (1.f - b2) * s * s;
   m[i] = mi;
   v[i] = vi;
   p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
@@ -540,13 +546,11 @@ hipError_t launch_prefilter_train(const RunArgs& a, const uint8_t* labels, float
   float* grad = reinterpret_cast<float*>(a.ws + a.L.pf_grad);
   hipLaunchKernelGGL(k_pf_reduce_chunks, dim3((N_P + 1 + 255) / 256, kPfChunks), dim3(256), 0, a.stream, A.partial,
                      (int)(grid * kPfWaves), a.out.status);
-  hipLaunchKernelGGL(k_pf_reduce, dim3((N_P + 1 + 255) / 256), dim3(256), 0, a.stream, A.partial,
-                     (int)(grid * kPfWaves), grad, loss_dev, a.out.status);
   const double b1 = 0.9, b2 = 0.999;
   const float c1 = (float)(1.0 - std::pow(b1, (double)step)), c2 = (float)(1.0 - std::pow(b2, (double)step));
   float* p = a.ctx->dev_pf;
-  hipLaunchKernelGGL(k_pf_adam, dim3((N_P + 255) / 256), dim3(256), 0, a.stream, p, p + N_P, p + 2 * N_P, grad, lr,
-                     (float)b1, (float)b2, 1e-8f, c1, c2, a.out.status);
+  hipLaunchKernelGGL(k_pf_update, dim3((N_P + 1 + 63) / 64), dim3(64), 0, a.stream, A.partial, (int)(grid * kPfWaves), grad,
+                     loss_dev, p, p + N_P, p + 2 * N_P, lr, (float)b1, (float)b2, 1e-8f, c1, c2, a.out.status);
   return hipGetLastError();
 }
 
