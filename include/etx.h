@@ -172,7 +172,8 @@ typedef enum {
   ETX_OPT_EDGE_WG_PER_CU = 1,/* persistent workgroups per CU of the edge kernels (1..8) */
   ETX_OPT_NODE_WG_PER_CU = 2,/* persistent workgroups per CU of the node kernels (1..8) */
   ETX_OPT_RADIUS_LDS = 3,    /* 1: stage and sort candidate windows in LDS when they fit; 0: always read HBM */
-  ETX_OPT_SEGSUM_UNROLL = 4, /* edge rows in flight per wave in the segmented sums: 1, 2, 4 or 8 */
+  ETX_OPT_SEGSUM_UNROLL = 4, /* edge rows in flight per wave in the segmented sums: 1, 2, 4 or 8 (batches of up to
+                                16,384 hits always keep eight) */
   ETX_OPT_PROFILE = 5,       /* 1: time every stage of eager runs with HIP events on the run's stream */
   ETX_OPT_EDGE_PIPELINE = 6, /* software pipeline of the per-edge kernels: 0 none, 1 prefetch the next
                                 tile's indices and edge rows, 2 also its node-product gathers */
@@ -192,8 +193,10 @@ typedef enum {
                                    widest axis into cells about r wide and searched as a cell list; smaller ones
                                    are scanned whole (default 512; 0: always bin) */
   ETX_OPT_FUSE_MESSAGES = 14,  /* 1: the node-update kernel gathers its messages itself (no separate message-sum
-                                  kernel, no message buffer round trip); same sums, same order, same bits */
-  ETX_OPT_RADIUS_FAST = 15,    /* 1: in staged windows, sources with at most 16 in-radius candidates are handled four
+                                  kernel, no message buffer round trip), and with a compact state of hidden
+                                  size 32 on graphs of few edges per hit it sums the short out-rows from the edge
+                                  rows instead of reading the edge kernels' sums; same sums, same order, same bits */
+  ETX_OPT_RADIUS_FAST = 15,    /* 1: in staged windows, sources with at most 16 in-radius candidates are handled eight
                                   to a wave; the others by the one-wave-per-source path; same bits */
   ETX_OPT_XCD_MAP = 16,        /* 1: the edge, message-sum and node kernels give each of the chip's eight XCDs a
                                   contiguous range of tiles, so that the node rows a region of the batch gathers stay
@@ -205,7 +208,8 @@ typedef enum {
                                   multiply-adds per edge; same bits) */
   ETX_OPT_CSC_PLACE = 18,      /* 1 (default): for events with short rows (< 16 edges per hit) the whole block drops
                                   the edges into their CSC columns through LDS cursors and then sorts every column by
-                                  edge index (source order); 0: one wave ranks 64 edges at a time; same permutation */
+                                  edge index (source order); 0: rows are walked in order, a range of rows per wave
+                                  with cursors of its own; same permutation */
   ETX_OPT_COMPACT_STATE = 19,  /* BF16 and FP8 runs only (FP32 and INT8 runs ignore it).  0 (default): the node encodings h and edge encodings e
                                   are kept in FP32 between kernels (residual master copies) and quantised only where
                                   they enter a GEMM.  1: both are stored in low precision (h as BF16; e in the
@@ -217,10 +221,9 @@ typedef enum {
                                   (ETX_VIEW_PF_FEAT; the workspace grows by 32 bytes per edge of capacity: set it
                                   before sizing the workspace); 0 (default): features are formed in registers only */
   ETX_OPT_RADIUS_SPLIT = 22    /* 1: the radius search runs as two launches over the (event, plane) units: candidate
-                                  windows of up to 512 hits (256 above embedding width 8) in workgroups with half the
-                                  staging LDS (three to a CU at embedding width up to 8), the larger ones as before;
-                                  each launch skips the other's units; the same bits (needs ETX_OPT_RADIUS_LDS = 1).
-                                  0 (default): one launch */
+                                  windows of up to 256 hits (512 with ETX_OPT_RADIUS_FAST) in workgroups of four waves
+                                  with less staging LDS, the larger ones as before; each launch skips the other's
+                                  units; the same bits (needs ETX_OPT_RADIUS_LDS = 1).  0 (default): one launch */
 } etx_option;
 etx_status etx_set_option(etx_ctx* ctx, int32_t key, int64_t value);
 etx_status etx_get_option(const etx_ctx* ctx, int32_t key, int64_t* value);
