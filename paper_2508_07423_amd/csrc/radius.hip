@@ -696,15 +696,14 @@ hipError_t launch_radius(const RunArgs& a, int mode, bool candidates) {
   // Few units (one event: one per plane) leave the chip idle while every wave
   // walks its sources, and the largest unit of an uneven batch outlasts the
   // others: up to eight workgroups share a unit, each staging the window itself.
-  // The more units, the more sources each must have to pay for that.  One trained
-  // full-size event 60 -> 11 us; 20 and 100 uneven events of a trained network (two
-  // and one workgroup per unit -> shared) 98 -> 48 and 176 -> 147 us, of a dense one
-  // 298 -> 117 and 654 -> 476 us; 400 (12,000 units) gain if dense (1.77 -> 1.51 ms)
-  // and lose if sparse (0.53 -> 0.55 ms).
+  // The more units, the more sources each must have to pay for that, and the
+  // fewer may share: a workgroup that finds nothing to do costs 0.8 ns (eight for
+  // each of 2,900 units of small events 33 -> 64 us).  One trained full-size event
+  // 60 -> 11 us; 20 uneven events of a trained network (two workgroups per unit ->
+  // shared) 98 -> 47 us, of a dense one 298 -> 117.
   const int64_t units = a.hits.n_events * c.n_planes;
-  A.parts = units <= 32 * (int64_t)a.ctx->n_cu ? 8 : 1;
+  auto parts = [&](int64_t per_cu) { return (int)std::max<int64_t>(1, std::min<int64_t>(8, per_cu * a.ctx->n_cu / units)); };
   A.part_sources = (int)std::max<int64_t>(1, std::min<int64_t>(128, units / 8));
-  dim3 grid((unsigned)units, (unsigned)A.parts);
   const bool small = c.emb_dim <= 8;
   A.stage_window = a.ctx->radius_lds;
   A.sort_min = a.ctx->radius_sort_min;
@@ -713,9 +712,13 @@ hipError_t launch_radius(const RunArgs& a, int mode, bool candidates) {
   const bool split = a.ctx->radius_split && A.stage_window;
   const bool fast = A.fast && mode == R_SELECT;
   A.split = !split ? 0 : fast ? RadiusShape<8, R_SMALL_FAST>::cap : RadiusShape<8, R_SMALL>::cap;
+  // the small shapes' units are small: two workgroups per CU at most share them
 #define LAUNCH_R(M_, D_, F_)                                                                              \
-  hipLaunchKernelGGL((k_radius<M_, D_, F_>), grid, dim3(RadiusShape<D_, F_>::threads),                    \
-                     (RadiusShape<D_, F_>::bytes), a.stream, A)
+  do {                                                                                                    \
+    A.parts = parts(F_ == R_LARGE ? 16 : 2);                                                              \
+    hipLaunchKernelGGL((k_radius<M_, D_, F_>), dim3((unsigned)units, (unsigned)A.parts),                  \
+                       dim3(RadiusShape<D_, F_>::threads), (RadiusShape<D_, F_>::bytes), a.stream, A);    \
+  } while (0)
 #define BY_MODE(D_)                                                  \
   if (split && fast) LAUNCH_R(R_SELECT, D_, R_SMALL_FAST);           \
   switch (mode) {                                                    \
