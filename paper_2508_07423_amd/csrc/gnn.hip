@@ -981,11 +981,19 @@ __device__ inline void gather_messages(const GnnArgs& A, int64_t node, bool vali
 // --------------------------------------------------------------------------
 // node update k (+ edge net k source/target products)
 // --------------------------------------------------------------------------
+// Waves per SIMD the registers have to leave room for.  FP8 with gathered messages
+// takes 132 to 140, which leaves one workgroup per CU: held to 128 (a few spills)
+// there are two, and 10,000 small events (H = 32) take 2.25 -> 1.72 ms in the node
+// updates, 1,000 full-size ones (H = 64) 4.45 -> 3.98.  BF16 at H = 64 (146) spills
+// too much for that (4.15 -> 4.74).
+template <int P, bool FUSE>
+constexpr int kNodeWaves = StorePrec<P>::value == P_FP8 && FUSE ? 4 : NodeThreads<P>::value / 256;
+
 // FUSE: the messages are gathered here (k_segsum is not launched).
 // NP: also write the node products h W_src and h W_dst of edge net k (else
 // the edge kernel forms them from the gathered rows of h).
 template <int H, int P, bool FUSE, bool NP>
-__global__ __launch_bounds__(NodeThreads<P>::value) void k_node_step(GnnArgs A) {
+__global__ __launch_bounds__(NodeThreads<P>::value, (kNodeWaves<P, FUSE>)) void k_node_step(GnnArgs A) {
   if (A.status[0] != 0) return;
   extern __shared__ float lds[];
   char* w = reinterpret_cast<char*>(lds);
