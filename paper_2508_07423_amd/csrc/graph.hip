@@ -437,10 +437,10 @@ constexpr int kCscThreads = 1024, kCscWaves = kCscThreads / 64;
 constexpr int kCscWords = 32768;                  // 128 KiB: two cursors per hit of the largest event
 static_assert(kCscWords >= 2 * ETX_MAX_EVENT_HITS, "two ranges of the largest event");
 // Batches of small events take half: as many ranges for an event of up to 1,024
-// hits, one of the largest (an event of over 8,192 walks).  Their workgroups, most
-// of them without work, need not wait for a CU whose whole LDS is free behind the
-// kernels of a batch on another stream (6,489 events of a trained network, two
-// batches in turn 7.32 -> 7.02 ms each).
+// hits, one of the largest (and an event whose longest column does not fit beside
+// its cursors walks).  Their workgroups, most of them without work, need not wait
+// for a CU whose whole LDS is free behind the kernels of a batch on another stream
+// (6,489 events of a trained network, two batches in turn 7.32 -> 7.02 ms each).
 constexpr int kCscFewWords = 16384;
 constexpr int kCscFewHits = 1024;                 // hits per event on average
 static_assert(kCscFewWords >= ETX_MAX_EVENT_HITS, "one range of the largest event");
@@ -454,7 +454,7 @@ __global__ __launch_bounds__(kCscThreads) void k_csc_wide(const int64_t* __restr
                                                           int place, int every_event, int words,
                                                           const int64_t* status) {
   extern __shared__ int cur[];                    // [ranges][n] cursors, or n cursors and the placed edges
-  __shared__ int tot[2][kCscWaves];
+  __shared__ int tot[2][kCscWaves], longest;
   if (status[0] != 0) return;
   const int ev = blockIdx.x, t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -467,11 +467,11 @@ __global__ __launch_bounds__(kCscThreads) void k_csc_wide(const int64_t* __restr
     if (t == 0) col_ptr[a] = ee;
     return;
   }
-  // a column may hold n edges, which have to fit beside the n cursors
-  const bool placed = place && edges < (int64_t)kCscRowWalk * n && 2 * n <= words;
+  bool placed = place && edges < (int64_t)kCscRowWalk * n;
   const int R = placed ? 1 : min(kCscWaves, words / n);
   const int per = (n + R - 1) / R;                // rows per range
   for (int i = t; i < R * n; i += kCscThreads) cur[i] = 0;
+  if (t == 0) longest = 0;
   __syncthreads();
   // counts per (range, target)
   if (placed) {
@@ -491,12 +491,13 @@ __global__ __launch_bounds__(kCscThreads) void k_csc_wide(const int64_t* __restr
   }
   __syncthreads();
   // exclusive scan over targets, and over the ranges of a target
-  int base = 0, slot = 0;
+  int base = 0, slot = 0, most = 0;
   for (int i0 = 0; i0 < n; i0 += kCscThreads, slot ^= 1) {
     const int i = i0 + t;
     int sum = 0;
     if (i < n)
       for (int w = 0; w < R; ++w) sum += cur[w * n + i];
+    most = max(most, sum);
     const int inc = wave_inclusive_scan(sum);
     if (lane == 63) tot[slot][wave] = inc;
     __syncthreads();
@@ -516,7 +517,10 @@ __global__ __launch_bounds__(kCscThreads) void k_csc_wide(const int64_t* __restr
     }
   }
   if (t == 0) col_ptr[a + n] = ee;
+  if (placed && 2 * n > words) atomicMax(&longest, most);
   __syncthreads();
+  // a column has to fit beside the n cursors; a longer one's event walks, in one range
+  if (longest > words - n) placed = false;
   if (placed) {
     // cursor i is the start of column i until its edges are placed, its end
     // afterwards; as many columns at a time as their edges fit beside the cursors
