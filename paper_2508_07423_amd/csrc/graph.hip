@@ -359,11 +359,12 @@ __global__ void k_edge_off(const int64_t* __restrict__ hit_off, int64_t n_events
 // Events of few rows and edges in a batch with more events than the chip holds
 // are placed by small workgroups in memory (k_csc_place); all others by
 // 1024-thread workgroups with kCscWords of LDS (k_csc_wide), which place in LDS,
-// as many columns at a time as fit beside the cursors, and rank every edge within its column instead of
-// sorting columns (a column of sixty is then sixty short loops, not one long
-// one).  Both kernels are launched, each skips the
-// other's events; a batch of few events (at most one per CU) takes the wide
-// kernel alone, since it then waits for the latency of one event.
+// as many columns at a time as fit beside the cursors, and rank every edge within
+// its column instead of sorting columns (a column of sixty is then sixty short
+// loops, not one long one); an event with a column too long for that walks.  Both
+// kernels are launched, each skips the other's events; a batch of few events (at
+// most one per CU) takes the wide kernel alone, since it then waits for the
+// latency of one event.
 constexpr int kCscRowWalk = 16;
 
 // The per-event kernels that keep one LDS word per hit of the event run as
@@ -437,66 +438,36 @@ constexpr int kCscThreads = 1024, kCscWaves = kCscThreads / 64;
 constexpr int kCscWords = 32768;                  // 128 KiB: two cursors per hit of the largest event
 static_assert(kCscWords >= 2 * ETX_MAX_EVENT_HITS, "two ranges of the largest event");
 // Batches of small events take half: as many ranges for an event of up to 1,024
-// hits, one of the largest (and an event whose longest column does not fit beside
-// its cursors walks).  Their workgroups, most of them without work, need not wait
-// for a CU whose whole LDS is free behind the kernels of a batch on another stream
-// (6,489 events of a trained network, two batches in turn 7.32 -> 7.02 ms each).
+// hits, one of the largest.  Their workgroups, most of them without work, need not
+// wait for a CU whose whole LDS is free behind the kernels of a batch on another
+// stream (6,489 events of a trained network, two batches in turn 7.32 -> 7.02 ms
+// each).
 constexpr int kCscFewWords = 16384;
 constexpr int kCscFewHits = 1024;                 // hits per event on average
 static_assert(kCscFewWords >= ETX_MAX_EVENT_HITS, "one range of the largest event");
 static_assert(kCscFewWords >= kCscWaves * kCscFewHits, "every wave a range");
 
-// place: short rows may be placed; every_event: the place kernel is not launched
-__global__ __launch_bounds__(kCscThreads) void k_csc_wide(const int64_t* __restrict__ hit_off,
-                                                          const int64_t* __restrict__ row_ptr,
-                                                          const int32_t* __restrict__ dst,
-                                                          int64_t* __restrict__ col_ptr, int32_t* __restrict__ csc,
-                                                          int place, int every_event, int words,
-                                                          const int64_t* status) {
-  extern __shared__ int cur[];                    // [ranges][n] cursors, or n cursors and the placed edges
-  __shared__ int tot[2][kCscWaves], longest;
-  if (status[0] != 0) return;
-  const int ev = blockIdx.x, t = threadIdx.x, lane = t & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int64_t a = hit_off[ev];
-  const int n = (int)(hit_off[ev + 1] - a);
-  const int64_t eb = row_ptr[a], ee = row_ptr[a + n];
-  const int64_t edges = ee - eb;
-  if (!every_event && place && csc_small(n, edges)) return;
-  if (n == 0) {
-    if (t == 0) col_ptr[a] = ee;
-    return;
-  }
-  bool placed = place && edges < (int64_t)kCscRowWalk * n;
-  const int R = placed ? 1 : min(kCscWaves, words / n);
-  const int per = (n + R - 1) / R;                // rows per range
-  for (int i = t; i < R * n; i += kCscThreads) cur[i] = 0;
-  if (t == 0) longest = 0;
-  __syncthreads();
-  // counts per (range, target)
-  if (placed) {
-    for (int64_t q = eb + t; q < ee; q += kCscThreads) atomicAdd(&cur[dst[q] - (int)a], 1);
-  } else if (wave < R) {
-    const int64_t q1 = row_ptr[a + min(n, (wave + 1) * per)];
-    int* c = cur + wave * n;
-    constexpr int kBatch = 8;
-    for (int64_t q = row_ptr[a + min(n, wave * per)] + lane; q < q1; q += 64 * kBatch) {
-      int d[kBatch];
-#pragma unroll
-      for (int u = 0; u < kBatch; ++u) d[u] = q + 64 * u < q1 ? dst[q + 64 * u] - (int)a : -1;
-#pragma unroll
-      for (int u = 0; u < kBatch; ++u)
-        if (d[u] >= 0) atomicAdd(&c[d[u]], 1);
-    }
-  }
-  __syncthreads();
-  // exclusive scan over targets, and over the ranges of a target
-  int base = 0, slot = 0, most = 0;
-  for (int i0 = 0; i0 < n; i0 += kCscThreads, slot ^= 1) {
+struct CscEvent {
+  int64_t a, eb, ee;                              // first hit; edges
+  int n;                                          // hits
+  const int64_t* row_ptr;
+  const int32_t* dst;
+  int64_t* col_ptr;
+  int32_t* csc;
+};
+
+// Counts of m columns (from hit `first` on) in R ranges -> cursors: an exclusive
+// scan over columns and the ranges of each, from `base` on, which moves past them.
+// Writes the columns' starts; returns the thread's longest column.
+__device__ inline int csc_scan(const CscEvent& E, int* cur, int first, int m, int R, int& base,
+                               int (&tot)[2][kCscWaves]) {
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  int slot = 0, most = 0;
+  for (int i0 = 0; i0 < m; i0 += kCscThreads, slot ^= 1) {
     const int i = i0 + t;
     int sum = 0;
-    if (i < n)
-      for (int w = 0; w < R; ++w) sum += cur[w * n + i];
+    if (i < m)
+      for (int w = 0; w < R; ++w) sum += cur[w * m + i];
     most = max(most, sum);
     const int inc = wave_inclusive_scan(sum);
     if (lane == 63) tot[slot][wave] = inc;
@@ -507,70 +478,116 @@ __global__ __launch_bounds__(kCscThreads) void k_csc_wide(const int64_t* __restr
       at += w < wave ? tot[slot][w] : 0;
       base += tot[slot][w];
     }
-    if (i < n) {
-      col_ptr[a + i] = eb + at;
+    if (i < m) {
+      E.col_ptr[E.a + first + i] = E.eb + at;
       for (int w = 0; w < R; ++w) {
-        const int c = cur[w * n + i];
-        cur[w * n + i] = at;
+        const int c = cur[w * m + i];
+        cur[w * m + i] = at;
         at += c;
       }
     }
   }
-  if (t == 0) col_ptr[a + n] = ee;
-  if (placed && 2 * n > words) atomicMax(&longest, most);
-  __syncthreads();
-  // a column has to fit beside the n cursors; a longer one's event walks, in one range
-  if (longest > words - n) placed = false;
-  if (placed) {
+  return most;
+}
+
+// Place: as many columns at a time as half the LDS holds cursors for (all of an
+// event's, or in half the LDS those of 8,192 hits), so that the other half is left
+// for their edges whatever the event's size.  With cursors for all columns an
+// event of 16,384 hits had no room and walked in one range: 300 small sparse
+// events and one such, 3.6 edges per hit, 3.54 ms, now 0.47 (1.5 edges per hit
+// 3.34 and 0.11).  False when a column's edges do not fit.
+__device__ inline bool csc_place_wide(const CscEvent& E, int* cur, int words, int (&tot)[2][kCscWaves], int& longest) {
+  const int t = threadIdx.x;
+  const int cols = min(E.n, words / 2), room = words - cols;
+  int* list = cur + cols;
+  int base = 0;
+  for (int first = 0; first < E.n; first += cols) {
+    const int m = min(cols, E.n - first), h0 = (int)E.a + first;
+    for (int i = t; i < m; i += kCscThreads) cur[i] = 0;
+    if (t == 0) longest = 0;
+    __syncthreads();
+    for (int64_t q = E.eb + t; q < E.ee; q += kCscThreads) {
+      const int d = E.dst[q] - h0;
+      if (d >= 0 && d < m) atomicAdd(&cur[d], 1);
+    }
+    __syncthreads();
+    const int most = csc_scan(E, cur, first, m, 1, base, tot);
+    if (room < E.n) atomicMax(&longest, most);
+    __syncthreads();
+    if (longest > room) return false;
     // cursor i is the start of column i until its edges are placed, its end
     // afterwards; as many columns at a time as their edges fit beside the cursors
-    int* list = cur + n;
-    const int room = words - n;
-    for (int lo = 0; lo < n;) {
+    for (int lo = 0; lo < m;) {
       const int begin = cur[lo];
-      int hi = n;
-      if ((int)edges - begin > room) {
+      int hi = m;
+      if (base - begin > room) {
         int x = lo + 1;                           // the last i with cur[i] <= begin + room
-        for (int step = n - x; x < hi - 1; step = (hi - x) / 2) {
-          const int m = min(hi - 1, x + max(1, step));
-          if (cur[m] - begin <= room) x = m;
-          else hi = m;
+        for (int step = m - x; x < hi - 1; step = (hi - x) / 2) {
+          const int k = min(hi - 1, x + max(1, step));
+          if (cur[k] - begin <= room) x = k;
+          else hi = k;
         }
         hi = x;
       }
-      const int end = hi < n ? cur[hi] : (int)edges;
+      const int end = hi < m ? cur[hi] : base;
       __syncthreads();                            // every thread has read the starts
-      for (int64_t q = eb + t; q < ee; q += kCscThreads) {
-        const int d = dst[q] - (int)a;
-        if (d >= lo && d < hi) list[atomicAdd(&cur[d], 1) - begin] = (int)(q - eb);
+      for (int64_t q = E.eb + t; q < E.ee; q += kCscThreads) {
+        const int d = E.dst[q] - h0;
+        if (d >= lo && d < hi) list[atomicAdd(&cur[d], 1) - begin] = (int)(q - E.eb);
       }
       __syncthreads();
       // an edge's place is the number of smaller ones in its column
       for (int j = t; j < end - begin; j += kCscThreads) {
-        const int e = list[j], d = dst[eb + e] - (int)a;
+        const int e = list[j], d = E.dst[E.eb + e] - h0;
         const int c0 = (d > lo ? cur[d - 1] : begin) - begin, c1 = cur[d] - begin;
         int rank = 0;
         for (int k = c0; k < c1; ++k) rank += list[k] < e ? 1 : 0;
-        csc[eb + begin + c0 + rank] = (int32_t)(eb + e);
+        E.csc[E.eb + begin + c0 + rank] = (int32_t)(E.eb + e);
       }
       __syncthreads();
       lo = hi;
     }
-    return;
   }
+  return true;
+}
+
+__device__ inline void csc_walk(const CscEvent& E, int* cur, int words, int (&tot)[2][kCscWaves]) {
+  const int t = threadIdx.x, lane = t & 63, n = E.n;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int R = min(kCscWaves, words / n);
+  const int per = (n + R - 1) / R;                // rows per range
+  const int r0 = min(n, wave * per), r1 = min(n, r0 + per);
+  int* c = cur + wave * n;
+  for (int i = t; i < R * n; i += kCscThreads) cur[i] = 0;
+  __syncthreads();
+  // counts per (range, target)
+  if (wave < R) {
+    const int64_t q1 = E.row_ptr[E.a + r1];
+    constexpr int kBatch = 8;
+    for (int64_t q = E.row_ptr[E.a + r0] + lane; q < q1; q += 64 * kBatch) {
+      int d[kBatch];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) d[u] = q + 64 * u < q1 ? E.dst[q + 64 * u] - (int)E.a : -1;
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u)
+        if (d[u] >= 0) atomicAdd(&c[d[u]], 1);
+    }
+  }
+  __syncthreads();
+  int base = 0;
+  csc_scan(E, cur, 0, n, R, base, tot);
+  __syncthreads();
   if (wave >= R) return;
   // Row bounds and targets are loaded kRow rows ahead so that their latency
   // overlaps the LDS updates.
   constexpr int kRow = 8;
-  const int r0 = min(n, wave * per), r1 = min(n, r0 + per);
-  int* c = cur + wave * n;
   int64_t rb[kRow + 1];
   int dd[kRow];
   auto load_block = [&](int i0, int64_t (&b)[kRow + 1], int (&d)[kRow]) {
 #pragma unroll
-    for (int q = 0; q <= kRow; ++q) b[q] = row_ptr[a + min(i0 + q, r1)];
+    for (int q = 0; q <= kRow; ++q) b[q] = E.row_ptr[E.a + min(i0 + q, r1)];
 #pragma unroll
-    for (int q = 0; q < kRow; ++q) d[q] = (b[q] + lane < b[q + 1]) ? dst[b[q] + lane] : 0;
+    for (int q = 0; q < kRow; ++q) d[q] = (b[q] + lane < b[q + 1]) ? E.dst[b[q] + lane] : 0;
   };
   if (r0 < r1) load_block(r0, rb, dd);
   for (int i0 = r0; i0 < r1; i0 += kRow) {
@@ -580,10 +597,10 @@ __global__ __launch_bounds__(kCscThreads) void k_csc_wide(const int64_t* __restr
 #pragma unroll
     for (int q = 0; q < kRow; ++q) {
       if (rb[q] + lane < rb[q + 1]) {
-        const int dl = dd[q] - (int)a;
+        const int dl = dd[q] - (int)E.a;
         const int pos = c[dl];
         c[dl] = pos + 1;
-        csc[eb + pos] = (int32_t)(rb[q] + lane);
+        E.csc[E.eb + pos] = (int32_t)(rb[q] + lane);
       }
       wave_sync();
     }
@@ -594,6 +611,28 @@ __global__ __launch_bounds__(kCscThreads) void k_csc_wide(const int64_t* __restr
       for (int q = 0; q < kRow; ++q) dd[q] = nd[q];
     }
   }
+}
+
+// place: short rows may be placed; every_event: the place kernel is not launched
+__global__ __launch_bounds__(kCscThreads) void k_csc_wide(const int64_t* __restrict__ hit_off,
+                                                          const int64_t* __restrict__ row_ptr,
+                                                          const int32_t* __restrict__ dst,
+                                                          int64_t* __restrict__ col_ptr, int32_t* __restrict__ csc,
+                                                          int place, int every_event, int words,
+                                                          const int64_t* status) {
+  extern __shared__ int cur[];                    // cursors, and the placed edges
+  __shared__ int tot[2][kCscWaves], longest;
+  if (status[0] != 0) return;
+  const int ev = blockIdx.x;
+  const int64_t a = hit_off[ev];
+  const int n = (int)(hit_off[ev + 1] - a);
+  const CscEvent E{a, row_ptr[a], row_ptr[a + n], n, row_ptr, dst, col_ptr, csc};
+  const int64_t edges = E.ee - E.eb;
+  if (!every_event && place && csc_small(n, edges)) return;
+  if (threadIdx.x == 0) col_ptr[a + n] = E.ee;
+  if (n == 0) return;
+  if (place && edges < (int64_t)kCscRowWalk * n && csc_place_wide(E, cur, words, tot, longest)) return;
+  csc_walk(E, cur, words, tot);
 }
 
 // --------------------------------------------------------------------------

@@ -1,0 +1,73 @@
+"""The (dst, src) permutation where its workgroups change form within a batch:
+a large sparse event among many small ones, columns as long as the event, and
+large events of few edges in batches of any size.  The permutation is compared
+with numpy's; a form that does not suit its event is told from the stage times
+of two batches of the same run."""
+import numpy as np
+import pytest
+
+from paper_2508_07423_amd import synth
+from tests.test_gpu_graph_sizes import MANY, _batch, _event
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def _csc_ms(etx, p, b, cap=None):
+    """Time of the CSC stage: the best of five runs."""
+    etx.etx_set_option(p.ctx, etx.ETX_OPT_PROFILE, 1)
+    best = np.inf
+    for _ in range(6):
+        etx.etx_profile_reset(p.ctx)
+        p.run(b, cap)
+        best = min(best, etx.etx_profile_read(p.ctx)["csc"][0])
+    etx.etx_set_option(p.ctx, etx.ETX_OPT_PROFILE, 0)
+    return best
+
+
+def _check_permutation(etx, p, b, batch):
+    res = p.results(b)
+    order = np.lexsort((res["src"], res["dst"]))
+    assert np.array_equal(p.view(b, etx.ETX_VIEW_CSC_EDGE, torch.int32).cpu().numpy()[:len(order)], order)
+    assert np.array_equal(p.view(b, etx.ETX_VIEW_COL_PTR, torch.int64).cpu().numpy(),
+                          np.searchsorted(res["dst"][order], np.arange(b.n_hits + 1)))
+    return res
+
+
+def test_large_sparse_event_among_small_ones():
+    """One event of 16,384 hits takes about as long among 300 small ones as alone: at most twice the passes over its
+    edges (half the LDS), where one wave walking its rows takes an order of magnitude longer."""
+    from paper_2508_07423_amd import etx
+    w = synth.C1.with_(k_max=6, gnn_steps=1)
+    p = etx.Pipeline(w, synth.xavier_weights(w))
+    alone, among = (_csc_ms(etx, p, etx.to_device(_batch(s))) for s in ([16384], MANY + [16384]))
+    p.close()
+    assert among < 3 * alone, (among, alone)
+
+
+def _hub_event(n, targets):
+    """n hits on two planes, `targets` of them on the second: columns of about n / targets edges."""
+    ev = _event(n, 5)
+    ev["plane"] = np.where(np.arange(n) % max(n // targets, 1) == 0, 1, 0).astype(np.int32)
+    while ev["plane"].sum() > targets:
+        ev["plane"][np.flatnonzero(ev["plane"])[-1]] = 0
+    return ev
+
+
+# columns of 400 edges and of about half the LDS (8,192); one column of nearly the whole event
+@pytest.mark.parametrize("place", [0, 1])
+@pytest.mark.parametrize("n,targets", [(9000, 20), (16384, 40), (16384, 2), (12000, 1), (16384, 1), (4097, 1)])
+def test_long_columns(n, targets, place):
+    from paper_2508_07423_amd import etx
+    w = synth.C1.with_(k_max=1, radius=50.0, gnn_steps=1)
+    small, hub = _batch(MANY), _hub_event(n, targets)
+    batch = {k: np.concatenate([small[k], hub[k]]) for k in hub}
+    batch["hit_off"] = np.concatenate([small["hit_off"], [small["hit_off"][-1] + n]])
+    b = etx.to_device(batch)
+    p = etx.Pipeline(w, synth.xavier_weights(w))
+    etx.etx_set_option(p.ctx, etx.ETX_OPT_CSC_PLACE, place)
+    p.run(b)
+    res = _check_permutation(etx, p, b, batch)
+    p.close()
+    columns = np.bincount(res["dst"], minlength=b.n_hits)[-n:]
+    assert columns.max() >= (n - targets) // targets
