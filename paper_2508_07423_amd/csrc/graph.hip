@@ -339,9 +339,9 @@ __global__ void k_edge_off(const int64_t* __restrict__ hit_off, int64_t n_events
 // The permutation of an event is built by one workgroup, in (dst, src) order
 // whichever way:
 //
-// - Walk (long rows, at least kCscRowWalk edges per source on average): the
-//   rows are cut into contiguous ranges, one per wave, each with its own LDS
-//   cursor per target.  The waves count their edges per target, a scan over
+// - Walk (long rows, at least kCscRowWalk edges per source on average, or all rows
+//   where placing is off): the rows are cut into contiguous ranges, one per wave,
+//   each with its own LDS cursor per target.  The waves count their edges per target, a scan over
 //   (target, range) turns the counts into cursors, and every wave walks its
 //   rows in order, a row per step (the targets of a row are distinct, so its
 //   lanes never share a cursor).  The chain of LDS updates of one wave is what
@@ -366,6 +366,13 @@ __global__ void k_edge_off(const int64_t* __restrict__ hit_off, int64_t n_events
 // most one per CU) takes the wide kernel alone, since it then waits for the
 // latency of one event.
 constexpr int kCscRowWalk = 16;
+// Walked events of over 2,048 hits (fewer than sixteen ranges) and fewer edges per
+// hit than this take 64 edges per step, not a row: a row step is about a quarter
+// microsecond, a step of 64 edges two.  300 events of 8,192 and of 16,384 hits, 1.8
+// edges per hit, 0.93 -> 0.28 and 3.60 -> 1.00 ms; one of 16,384 with 5.4 edges per
+// hit 1.92 by rows and 1.39 so, but 4,096 hits 0.131 and 0.126, 2,000 hits 0.042 and
+// 0.060: shorter ranges than that have too few steps.
+constexpr int kCscChunkRow = 4;
 
 // The per-event kernels that keep one LDS word per hit of the event run as
 // two launches: events of up to kSmallEventHits hits in workgroups with 16 KiB
@@ -578,6 +585,33 @@ __device__ inline void csc_walk(const CscEvent& E, int* cur, int words, int (&to
   csc_scan(E, cur, 0, n, R, base, tot);
   __syncthreads();
   if (wave >= R) return;
+  if (R < kCscWaves && E.ee - E.eb < (int64_t)kCscChunkRow * n) {
+    // Very short rows in long ranges, 64 edges per step whatever rows they are of:
+    // a lane's rank among the lanes with the same target (lower lanes are earlier
+    // edges) gives its slot after the target's cursor, and the last of them moves
+    // the cursor.  The next step's targets load meanwhile.
+    const int64_t q0 = E.row_ptr[E.a + r0], q1 = E.row_ptr[E.a + r1];
+    int next = q0 + lane < q1 ? E.dst[q0 + lane] - (int)E.a : -1;
+    for (int64_t q = q0 + lane; q - lane < q1; q += 64) {
+      const int d = next;
+      next = q + 64 < q1 ? E.dst[q + 64] - (int)E.a : -1;
+      int rank = 0, count = 0;
+#pragma unroll
+      for (int k = 0; k < 64; ++k) {
+        const bool same = __builtin_amdgcn_readlane(d, k) == d;
+        count += same ? 1 : 0;
+        rank += same && k < lane ? 1 : 0;
+      }
+      const int pos = d >= 0 ? c[d] + rank : 0;
+      wave_sync();
+      if (d >= 0) {
+        E.csc[E.eb + pos] = (int32_t)q;
+        if (rank == count - 1) c[d] = pos + 1;
+      }
+      wave_sync();
+    }
+    return;
+  }
   // Row bounds and targets are loaded kRow rows ahead so that their latency
   // overlaps the LDS updates.
   constexpr int kRow = 8;

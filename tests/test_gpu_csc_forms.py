@@ -71,3 +71,36 @@ def test_long_columns(n, targets, place):
     p.close()
     columns = np.bincount(res["dst"], minlength=b.n_hits)[-n:]
     assert columns.max() >= (n - targets) // targets
+
+
+def test_short_rows_walk_by_edges():
+    """Without placing, a walked event of few edges takes time with its edges, not its rows: with k_max 2 it has less
+    than half the edges of k_max 6."""
+    from paper_2508_07423_amd import etx
+    batch = _batch([16384, 16384])
+    b = etx.to_device(batch)
+    ms, edges = [], []
+    for k_max in (2, 6):
+        w = synth.C1.with_(k_max=k_max, gnn_steps=1)
+        p = etx.Pipeline(w, synth.xavier_weights(w))
+        etx.etx_set_option(p.ctx, etx.ETX_OPT_CSC_PLACE, 0)
+        ms.append(_csc_ms(etx, p, b))
+        edges.append(len(_check_permutation(etx, p, b, batch)["src"]))
+        p.close()
+    assert edges[0] < 0.5 * edges[1]
+    assert ms[0] < 0.75 * ms[1], ms
+
+
+# events on both sides of 2,048 hits and of four edges per hit
+@pytest.mark.parametrize("sizes,k_max", [([2048, 2049, 2050], 3), ([2049, 4100, 0, 63], 4), ([16384, 8193], 5),
+                                         ([4096, 2500], 9), ([16384], 1)])
+def test_short_rows_walked(sizes, k_max):
+    from paper_2508_07423_amd import etx
+    w = synth.C1.with_(k_max=k_max, gnn_steps=1)
+    batch = _batch(sizes)
+    b = etx.to_device(batch)
+    p = etx.Pipeline(w, synth.xavier_weights(w))
+    etx.etx_set_option(p.ctx, etx.ETX_OPT_CSC_PLACE, 0)
+    p.run(b)
+    _check_permutation(etx, p, b, batch)
+    p.close()
