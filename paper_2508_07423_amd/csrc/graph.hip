@@ -263,9 +263,14 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_small(const int32_t* __re
                                                              const int64_t* __restrict__ hit_off, int64_t n_events,
                                                              int64_t* __restrict__ edge_off, int64_t* status) {
   __shared__ int tot[kScanThreads / 64];
-  __shared__ int64_t sums[2][kScanThreads / 64];
+  __shared__ int64_t sums[3][kScanThreads / 64];
   __shared__ int64_t bad;
-  if (status[0] != 0) return;
+  // The last workgroup reports too many edges while others may still start, so a
+  // workgroup's waves can read different values here: they all go on, and agree on
+  // what they read where they add up their sums.  (One workgroup alone reports after
+  // all its waves have read.)
+  const int64_t found = status[0];
+  if (gridDim.x == 1 && found != 0) return;
   const int t = threadIdx.x, lane = t & 63;
   const int64_t i0 = (int64_t)blockIdx.x * kScanBlock, i1 = i0 + kScanBlock;
   const bool last = blockIdx.x + 1 == gridDim.x;
@@ -296,14 +301,18 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_small(const int32_t* __re
     if (lane == 0) {
       sums[0][t >> 6] = before;
       sums[1][t >> 6] = all;
+      sums[2][t >> 6] = found;
     }
     __syncthreads();
     before = all = 0;
+    int64_t error = 0;
 #pragma unroll
     for (int w = 0; w < kScanThreads / 64; ++w) {
       before += sums[0][w];
       all += sums[1][w];
+      error |= sums[2][w];
     }
+    if (error != 0) return;
   }
   // more edges than fit: only the last workgroup reports it, none writes offsets
   const bool fits = gridDim.x == 1 || (all <= capacity && all < 0x7fffffffLL);
