@@ -931,9 +931,10 @@ __device__ inline void gather_messages(const GnnArgs& A, int64_t node, bool vali
   int id[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) id[u] = m.id0[u];
-  // the first in-rows are in flight while the out-sum is formed (FP32 rows take
-  // too many registers for that)
-  constexpr bool AHEAD = StorePrec<P>::value != P_F32;
+  // the first in-rows are in flight while the out-sum is formed (BF16; FP32 rows take
+  // too many registers for that, and the FP8 kernel, held to 128, spills more:
+  // 2.4 edges per hit 0.86 ms with, 0.82 without, 11.9 per hit 2.07 and 1.87)
+  constexpr bool AHEAD = StorePrec<P>::value == P_BF16;
   RawE<P, H> raw[U];
   auto fetch_in = [&]() {
 #pragma unroll
@@ -983,9 +984,11 @@ __device__ inline void gather_messages(const GnnArgs& A, int64_t node, bool vali
 // --------------------------------------------------------------------------
 // Waves per SIMD the registers have to leave room for.  FP8 with gathered messages
 // takes 132 to 140, which leaves one workgroup per CU: held to 128 (a few spills)
-// there are two, and 10,000 small events (H = 32) take 2.25 -> 1.72 ms in the node
-// updates, 1,000 full-size ones (H = 64) 4.45 -> 3.98.  BF16 at H = 64 (146) spills
-// too much for that (4.15 -> 4.74).
+// there are two.  Node updates of 10,000 small events (H = 32) and 1,000 full-size
+// ones (H = 64), one workgroup -> two: 2.25 -> 1.69 and 4.45 -> 3.67 ms; with the
+// edge products written too, where the out-sums read from the edge kernels had
+// taken 2.93 and 6.52: 2.82 and 6.29.  BF16 at H = 64 (146) spills too much for that
+// (4.15 -> 4.74).
 template <int P, bool FUSE>
 constexpr int kNodeWaves = StorePrec<P>::value == P_FP8 && FUSE ? 4 : NodeThreads<P>::value / 256;
 
