@@ -243,7 +243,8 @@ const char* etx_stage_name(int32_t stage);   /* "" for an unknown stage */
  * under the batch's key: the configuration and run modes (precision, embedding
  * precision, compact state, prefilter) plus the shape bucket (hits per event
  * and events per batch, each rounded to the nearest power of two).  Appends the
- * trials to `json_path` (JSON lines; may be NULL).  Synchronises the stream.
+ * trials to `json_path` (JSON lines, each knob's trials and the stages that judge
+ * it; may be NULL).  Synchronises the stream.
  * The device status of the first trial is read back: an error there (edge
  * capacity, bad input) is returned, and the options in effect before the call
  * are restored, as after any failure. */
