@@ -237,6 +237,13 @@ extern "C" etx_status etx_autotune(etx_ctx* ctx, const etx_hits* hits, etx_out* 
                        ", \"precision\": " + std::to_string(ctx->cfg.precision) + ", \"choice\": {";
   for (size_t ki = 0; ki < knobs.size() && st == ETX_OK; ++ki) {
     const Knob& k = knobs[ki];
+    // Batches whose message sums don't follow the option (eight rows whatever it says,
+    // or none launched) would choose by noise, for larger ones of the same key: these
+    // get the default.
+    if (k.keys[0] == ETX_OPT_SEGSUM_UNROLL && (hits->n_hits <= kSegsumSmallHits || ctx->fuse_messages)) {
+      etx_set_option(ctx, ETX_OPT_SEGSUM_UNROLL, kSegsumUnroll);
+      continue;
+    }
     std::vector<int64_t> best_v;
     double best_t = 1e30;
     std::string trials;

@@ -1503,8 +1503,7 @@ hipError_t launch_segsum(const RunArgs& a, int k) {
   // A small batch leaves a SIMD too few waves to hide the chain of a node's rows: eight
   // are in flight (four before; one event of 481 hits 6.7 -> 5.2 us, one dense full-size
   // event 18 -> 14, three 25 -> 22, eight no gain; sixteen cost sparse events 0.6 us).
-  constexpr int64_t kSmallHits = 16384;
-  const int U = a.hits.n_hits <= kSmallHits ? 8 : a.ctx->segsum_unroll;
+  const int U = a.hits.n_hits <= kSegsumSmallHits ? 8 : a.ctx->segsum_unroll;
   // the sums read the stored edge rows: FP32 whenever the state is kept in FP32
   const int sp = (a.prec == P_BF16 || a.prec == P_FP8) ? a.prec : P_F32;
 #define SEG_U(U_) DISPATCH_HP(Hh, sp, hipLaunchKernelGGL((k_segsum<H, P, U_>), dim3(grid), dim3(256), 0, a.stream, A))

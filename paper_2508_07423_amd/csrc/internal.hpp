@@ -50,6 +50,12 @@ struct WsLayout {
   int64_t n_scan_blocks;
 };
 
+// Edge rows in flight per wave in the message sums: the default of
+// ETX_OPT_SEGSUM_UNROLL, and the batch size up to which eight are kept whatever
+// the option says.
+constexpr int kSegsumUnroll = 4;
+constexpr int64_t kSegsumSmallHits = 16384;
+
 struct GraphKey {
   const void* p[16];
   int64_t n[4];
@@ -84,7 +90,7 @@ struct etx_ctx {
   int edge_wg_per_cu = 8;
   int node_wg_per_cu = 1;
   int radius_lds = 1;
-  int segsum_unroll = 4;
+  int segsum_unroll = etx::kSegsumUnroll;
   int edge_pipeline = 1;
   int edge_threads = 256;
   int edge_wreg = 0;

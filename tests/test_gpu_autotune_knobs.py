@@ -43,3 +43,17 @@ def test_fused_messages_are_judged_by_what_they_change(name, precision, compact,
     order = list(choice)
     assert order.index("fuse_messages") < order.index("edge_threads_x_wg_per_cu")
     assert order.index("fuse_messages") < order.index("edge_pipeline")
+
+
+@pytest.mark.parametrize("name,tracks,events,small", [("c1", 50, 1, True), ("c3", 100, 8, True), ("c3", 100, 24, False)])
+def test_unroll_is_tuned_where_it_is_used(name, tracks, events, small, tmp_path):
+    """Batches of up to 16,384 hits keep eight rows in flight whatever the option, and fused runs launch no message
+    sums: no trials, and the stored entry holds the default."""
+    from paper_2508_07423_amd import etx
+    choice, entry, hits = _tune(synth.WORKLOADS[name], tracks, events, "ETX_FP32", 0, tmp_path, [("SEGSUM_UNROLL", 1)])
+    assert (hits <= 16384) == small
+    if small or choice["fuse_messages"] == "1":
+        assert "segsum_unroll" not in choice and entry[etx.ETX_OPT_SEGSUM_UNROLL] == 4
+    else:
+        assert int(choice["segsum_unroll"]) == entry[etx.ETX_OPT_SEGSUM_UNROLL]
+    assert "radius_sort_min" in choice
