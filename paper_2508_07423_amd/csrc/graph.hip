@@ -361,12 +361,12 @@ __global__ void k_edge_off(const int64_t* __restrict__ hit_off, int64_t n_events
 //   writes).
 // - Place (short rows): every thread drops edges into their columns through
 //   LDS cursors, any order within a column, then every column is sorted by edge
-//   index, which is source order (insertion sort: fewer than kCscRowWalk edges
-//   per column on average; 10,000 uneven events of a trained network 1.11 ->
-//   0.66 ms with the wide kernel for the events of over 4,096 hits).
+//   index, which is source order (10,000 uneven events of a trained network 1.11
+//   -> 0.66 ms with the wide kernel for the events of over 4,096 hits).
 //
 // Events of few rows and edges in a batch with more events than the chip holds
-// are placed by small workgroups in memory (k_csc_place); all others by
+// are placed by small workgroups in memory, with an insertion sort of every column
+// (k_csc_place); all others by
 // 1024-thread workgroups with kCscWords of LDS (k_csc_wide), which place in LDS,
 // as many columns at a time as fit beside the cursors, and rank every edge within
 // its column instead of sorting columns (a column of sixty is then sixty short
@@ -396,8 +396,13 @@ __device__ inline bool event_in_launch(int n) {
   return CAP == kSmallEventHits ? n <= kSmallEventHits : n > kSmallEventHits;
 }
 
+// Events that k_csc_place takes.  Sorting a column in memory is slower than the
+// wide workgroups' rank in LDS from about six edges per column on: 800 events of
+// 490 hits, 12 edges per hit, 0.166 ms in memory, 0.065 in LDS; 300 of 500 hits, 4.8
+// per hit, 0.027 and 0.028.
+constexpr int kCscSortRow = 6;
 __device__ inline bool csc_small(int n, int64_t edges) {
-  return n <= kSmallEventHits && edges < (int64_t)kCscRowWalk * n;
+  return n <= kSmallEventHits && edges < (int64_t)kCscSortRow * n;
 }
 
 __global__ __launch_bounds__(256) void k_csc_place(const int64_t* __restrict__ hit_off,

@@ -104,3 +104,35 @@ def test_short_rows_walked(sizes, k_max):
     p.run(b)
     _check_permutation(etx, p, b, batch)
     p.close()
+
+
+def test_small_dense_events_are_not_sorted_in_memory():
+    """800 events of about twelve edges per hit: the choice by row length is no slower than walking every event, which
+    takes them all in wide workgroups (half as much again allowed; sorting their columns in memory took 2.5 times)."""
+    from paper_2508_07423_amd import etx
+    w = synth.C1.with_(gnn_steps=1)
+    batch = synth.generate_batch(w, 800, first=1)
+    b = etx.to_device(batch)
+    p = etx.Pipeline(w, synth.xavier_weights(w))
+    p.run(b)
+    per_hit = len(_check_permutation(etx, p, b, batch)["src"]) / b.n_hits
+    assert 8 < per_hit < 16, per_hit
+    ms = []
+    for place in (0, 1):
+        etx.etx_set_option(p.ctx, etx.ETX_OPT_CSC_PLACE, place)
+        ms.append(_csc_ms(etx, p, b))
+    p.close()
+    assert ms[1] < 1.6 * ms[0], ms
+
+
+# events on both sides of six edges per hit in one batch of more events than CUs, up to 4,096 hits and above
+@pytest.mark.parametrize("k_max", [5, 6, 7, 8, 12])
+def test_rows_around_the_sorted_length(k_max):
+    from paper_2508_07423_amd import etx
+    w = synth.C1.with_(k_max=k_max, gnn_steps=1)
+    batch = _batch(MANY + [2000, 4095, 4096, 4097, 700, 0, 1])
+    b = etx.to_device(batch)
+    p = etx.Pipeline(w, synth.xavier_weights(w))
+    p.run(b)
+    _check_permutation(etx, p, b, batch)
+    p.close()
