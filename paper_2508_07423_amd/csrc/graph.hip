@@ -365,8 +365,8 @@ __global__ void k_edge_off(const int64_t* __restrict__ hit_off, int64_t n_events
 //   -> 0.66 ms with the wide kernel for the events of over 4,096 hits).
 //
 // Events of few rows and edges in a batch with more events than the chip holds
-// are placed by small workgroups in memory, with an insertion sort of every column
-// (k_csc_place); all others by
+// are placed by small workgroups in memory, with an insertion sort of every column, or
+// walked by them (k_csc_small); all others by
 // 1024-thread workgroups with kCscWords of LDS (k_csc_wide), which place in LDS,
 // as many columns at a time as fit beside the cursors, and rank every edge within
 // its column instead of sorting columns (a column of sixty is then sixty short
@@ -396,63 +396,18 @@ __device__ inline bool event_in_launch(int n) {
   return CAP == kSmallEventHits ? n <= kSmallEventHits : n > kSmallEventHits;
 }
 
-// Events that k_csc_place takes.  Sorting a column in memory is slower than the
-// wide workgroups' rank in LDS from about six edges per column on: 800 events of
-// 490 hits, 12 edges per hit, 0.166 ms in memory, 0.065 in LDS; 300 of 500 hits, 4.8
-// per hit, 0.027 and 0.028.
+// Events that k_csc_small takes.
+// place: sorting a column in memory is slower than the wide workgroups' rank in LDS
+// from about six edges per column on: 800 events of 490 hits, 12 edges per hit,
+// 0.166 ms in memory, 0.065 in LDS; 300 of 500 hits, 4.8 per hit, 0.027 and 0.028.
+// walk: events whose few edges leave sixteen waves little to do, in batches of such
+// (kCscFewHits): 4,000 of 490 hits, 2 edges per hit, 0.195 ms in wide workgroups, one to
+// a CU, 0.102 in small ones; of 700 hits 0.31 and 0.18.
 constexpr int kCscSortRow = 6;
-__device__ inline bool csc_small(int n, int64_t edges) {
-  return n <= kSmallEventHits && edges < (int64_t)kCscSortRow * n;
-}
-
-__global__ __launch_bounds__(256) void k_csc_place(const int64_t* __restrict__ hit_off,
-                                                   const int64_t* __restrict__ row_ptr,
-                                                   const int32_t* __restrict__ dst, int64_t* __restrict__ col_ptr,
-                                                   int32_t* __restrict__ csc, const int64_t* status) {
-  if (status[0] != 0) return;
-  __shared__ int cur[kSmallEventHits];
-  __shared__ int tmp[4];
-  const int ev = blockIdx.x, t = threadIdx.x;
-  const int64_t a = hit_off[ev];
-  const int n = (int)(hit_off[ev + 1] - a);
-  const int64_t eb = row_ptr[a], ee = row_ptr[a + n];
-  if (!csc_small(n, ee - eb)) return;
-  for (int i = t; i < n; i += 256) cur[i] = 0;
-  __syncthreads();
-  for (int64_t q = eb + t; q < ee; q += 256) atomicAdd(&cur[dst[q] - a], 1);
-  __syncthreads();
-  int base = 0;
-  for (int i0 = 0; i0 < n; i0 += 256) {
-    int i = i0 + t;
-    int v = i < n ? cur[i] : 0;
-    int total;
-    int ex = block_exclusive_scan(v, tmp, total);
-    if (i < n) {
-      cur[i] = base + ex;
-      col_ptr[a + i] = eb + base + ex;
-    }
-    base += total;
-  }
-  if (t == 0) col_ptr[a + n] = ee;
-  __syncthreads();
-  for (int64_t q = eb + t; q < ee; q += 256) {
-    const int pos = atomicAdd(&cur[dst[q] - (int)a], 1);
-    csc[eb + pos] = (int32_t)q;
-  }
-  __syncthreads();
-  for (int i = t; i < n; i += 256) {
-    const int64_t c0 = col_ptr[a + i], c1 = col_ptr[a + i + 1];
-    for (int64_t j = c0 + 1; j < c1; ++j) {
-      const int32_t v = csc[j];
-      int64_t k = j - 1;
-      for (; k >= c0; --k) {
-        const int32_t u = csc[k];
-        if (u < v) break;
-        csc[k + 1] = u;
-      }
-      csc[k + 1] = v;
-    }
-  }
+constexpr int kCscFewHits = 1024;                 // hits per event on average
+__device__ inline bool csc_small(int n, int64_t edges, int place) {
+  return place ? n <= kSmallEventHits && edges < (int64_t)kCscSortRow * n
+               : n <= kCscFewHits && edges < (int64_t)kCscChunkRow * n;
 }
 
 constexpr int kCscThreads = 1024, kCscWaves = kCscThreads / 64;
@@ -464,7 +419,6 @@ static_assert(kCscWords >= 2 * ETX_MAX_EVENT_HITS, "two ranges of the largest ev
 // stream (6,489 events of a trained network, two batches in turn 7.32 -> 7.02 ms
 // each).
 constexpr int kCscFewWords = 16384;
-constexpr int kCscFewHits = 1024;                 // hits per event on average
 static_assert(kCscFewWords >= ETX_MAX_EVENT_HITS, "one range of the largest event");
 static_assert(kCscFewWords >= kCscWaves * kCscFewHits, "every wave a range");
 
@@ -479,12 +433,13 @@ struct CscEvent {
 
 // Counts of m columns (from hit `first` on) in R ranges -> cursors: an exclusive
 // scan over columns and the ranges of each, from `base` on, which moves past them.
-// Writes the columns' starts; returns the thread's longest column.
+// T threads.  Writes the columns' starts; returns the thread's longest column.
+template <int T>
 __device__ inline int csc_scan(const CscEvent& E, int* cur, int first, int m, int R, int& base,
-                               int (&tot)[2][kCscWaves]) {
+                               int (&tot)[2][T / 64]) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   int slot = 0, most = 0;
-  for (int i0 = 0; i0 < m; i0 += kCscThreads, slot ^= 1) {
+  for (int i0 = 0; i0 < m; i0 += T, slot ^= 1) {
     const int i = i0 + t;
     int sum = 0;
     if (i < m)
@@ -495,7 +450,7 @@ __device__ inline int csc_scan(const CscEvent& E, int* cur, int first, int m, in
     __syncthreads();
     int at = base + inc - sum;
 #pragma unroll
-    for (int w = 0; w < kCscWaves; ++w) {
+    for (int w = 0; w < T / 64; ++w) {
       at += w < wave ? tot[slot][w] : 0;
       base += tot[slot][w];
     }
@@ -532,7 +487,7 @@ __device__ inline bool csc_place_wide(const CscEvent& E, int* cur, int words, in
       if (d >= 0 && d < m) atomicAdd(&cur[d], 1);
     }
     __syncthreads();
-    const int most = csc_scan(E, cur, first, m, 1, base, tot);
+    const int most = csc_scan<kCscThreads>(E, cur, first, m, 1, base, tot);
     if (room < E.n) atomicMax(&longest, most);
     __syncthreads();
     if (longest > room) return false;
@@ -572,14 +527,16 @@ __device__ inline bool csc_place_wide(const CscEvent& E, int* cur, int words, in
   return true;
 }
 
-__device__ inline void csc_walk(const CscEvent& E, int* cur, int words, int (&tot)[2][kCscWaves]) {
+// T threads per workgroup
+template <int T>
+__device__ inline void csc_walk(const CscEvent& E, int* cur, int words, int (&tot)[2][T / 64]) {
   const int t = threadIdx.x, lane = t & 63, n = E.n;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int R = min(kCscWaves, words / n);
+  const int R = min(T / 64, words / n);
   const int per = (n + R - 1) / R;                // rows per range
   const int r0 = min(n, wave * per), r1 = min(n, r0 + per);
   int* c = cur + wave * n;
-  for (int i = t; i < R * n; i += kCscThreads) cur[i] = 0;
+  for (int i = t; i < R * n; i += T) cur[i] = 0;
   __syncthreads();
   // counts per (range, target)
   if (wave < R) {
@@ -596,10 +553,10 @@ __device__ inline void csc_walk(const CscEvent& E, int* cur, int words, int (&to
   }
   __syncthreads();
   int base = 0;
-  csc_scan(E, cur, 0, n, R, base, tot);
+  csc_scan<T>(E, cur, 0, n, R, base, tot);
   __syncthreads();
   if (wave >= R) return;
-  if (R < kCscWaves && E.ee - E.eb < (int64_t)kCscChunkRow * n) {
+  if (R < T / 64 && E.ee - E.eb < (int64_t)kCscChunkRow * n) {
     // Very short rows in long ranges, 64 edges per step whatever rows they are of:
     // a lane's rank among the lanes with the same target (lower lanes are earlier
     // edges) gives its slot after the target's cursor, and the last of them moves
@@ -662,7 +619,62 @@ __device__ inline void csc_walk(const CscEvent& E, int* cur, int words, int (&to
   }
 }
 
-// place: short rows may be placed; every_event: the place kernel is not launched
+__global__ __launch_bounds__(256) void k_csc_small(const int64_t* __restrict__ hit_off,
+                                                   const int64_t* __restrict__ row_ptr,
+                                                   const int32_t* __restrict__ dst, int64_t* __restrict__ col_ptr,
+                                                   int32_t* __restrict__ csc, int place, const int64_t* status) {
+  if (status[0] != 0) return;
+  __shared__ int cur[kSmallEventHits];
+  __shared__ int tmp[4], tot[2][4];
+  const int ev = blockIdx.x, t = threadIdx.x;
+  const int64_t a = hit_off[ev];
+  const int n = (int)(hit_off[ev + 1] - a);
+  const int64_t eb = row_ptr[a], ee = row_ptr[a + n];
+  if (!csc_small(n, ee - eb, place)) return;
+  if (!place) {
+    if (t == 0) col_ptr[a + n] = ee;
+    csc_walk<256>(CscEvent{a, eb, ee, n, row_ptr, dst, col_ptr, csc}, cur, kSmallEventHits, tot);
+    return;
+  }
+  for (int i = t; i < n; i += 256) cur[i] = 0;
+  __syncthreads();
+  for (int64_t q = eb + t; q < ee; q += 256) atomicAdd(&cur[dst[q] - a], 1);
+  __syncthreads();
+  int base = 0;
+  for (int i0 = 0; i0 < n; i0 += 256) {
+    int i = i0 + t;
+    int v = i < n ? cur[i] : 0;
+    int total;
+    int ex = block_exclusive_scan(v, tmp, total);
+    if (i < n) {
+      cur[i] = base + ex;
+      col_ptr[a + i] = eb + base + ex;
+    }
+    base += total;
+  }
+  if (t == 0) col_ptr[a + n] = ee;
+  __syncthreads();
+  for (int64_t q = eb + t; q < ee; q += 256) {
+    const int pos = atomicAdd(&cur[dst[q] - (int)a], 1);
+    csc[eb + pos] = (int32_t)q;
+  }
+  __syncthreads();
+  for (int i = t; i < n; i += 256) {
+    const int64_t c0 = col_ptr[a + i], c1 = col_ptr[a + i + 1];
+    for (int64_t j = c0 + 1; j < c1; ++j) {
+      const int32_t v = csc[j];
+      int64_t k = j - 1;
+      for (; k >= c0; --k) {
+        const int32_t u = csc[k];
+        if (u < v) break;
+        csc[k + 1] = u;
+      }
+      csc[k + 1] = v;
+    }
+  }
+}
+
+// place: short rows may be placed; every_event: the small kernel is not launched
 __global__ __launch_bounds__(kCscThreads) void k_csc_wide(const int64_t* __restrict__ hit_off,
                                                           const int64_t* __restrict__ row_ptr,
                                                           const int32_t* __restrict__ dst,
@@ -677,11 +689,11 @@ __global__ __launch_bounds__(kCscThreads) void k_csc_wide(const int64_t* __restr
   const int n = (int)(hit_off[ev + 1] - a);
   const CscEvent E{a, row_ptr[a], row_ptr[a + n], n, row_ptr, dst, col_ptr, csc};
   const int64_t edges = E.ee - E.eb;
-  if (!every_event && place && csc_small(n, edges)) return;
+  if (!every_event && csc_small(n, edges, place)) return;
   if (threadIdx.x == 0) col_ptr[a + n] = E.ee;
   if (n == 0) return;
   if (place && edges < (int64_t)kCscRowWalk * n && csc_place_wide(E, cur, words, tot, longest)) return;
-  csc_walk(E, cur, words, tot);
+  csc_walk<kCscThreads>(E, cur, words, tot);
 }
 
 // --------------------------------------------------------------------------
@@ -897,15 +909,15 @@ hipError_t launch_csc(const RunArgs& a) {
   if (a.hits.n_events == 0) return hipSuccess;
   const dim3 grid((unsigned)a.hits.n_events);
   const int place = a.ctx->csc_place;
-  const bool wide_only = !place || a.hits.n_events <= a.ctx->n_cu;
-  if (!wide_only)
-    hipLaunchKernelGGL(k_csc_place, grid, dim3(256), 0, a.stream, a.hits.hit_off, WS(a, row_ptr, int64_t), a.out.dst,
-                       WS(a, col_ptr, int64_t), WS(a, csc, int32_t), a.out.status);
-  const bool few_hits = !wide_only && a.hits.n_hits <= kCscFewHits * a.hits.n_events;
-  const int words = few_hits ? kCscFewWords : kCscWords;
+  const bool many = a.hits.n_events > a.ctx->n_cu, few_hits = many && a.hits.n_hits <= kCscFewHits * a.hits.n_events;
+  const bool small = place ? many : few_hits;
+  if (small)
+    hipLaunchKernelGGL(k_csc_small, grid, dim3(256), 0, a.stream, a.hits.hit_off, WS(a, row_ptr, int64_t), a.out.dst,
+                       WS(a, col_ptr, int64_t), WS(a, csc, int32_t), place, a.out.status);
+  const int words = place && few_hits ? kCscFewWords : kCscWords;
   hipLaunchKernelGGL(k_csc_wide, grid, dim3(kCscThreads), sizeof(int) * words, a.stream, a.hits.hit_off,
                      WS(a, row_ptr, int64_t), a.out.dst, WS(a, col_ptr, int64_t), WS(a, csc, int32_t), place,
-                     wide_only ? 1 : 0, words, a.out.status);
+                     small ? 0 : 1, words, a.out.status);
   return hipGetLastError();
 }
 

@@ -136,3 +136,37 @@ def test_rows_around_the_sorted_length(k_max):
     p.run(b)
     _check_permutation(etx, p, b, batch)
     p.close()
+
+
+def test_many_small_sparse_events_walked():
+    """Without placing, 4,000 events of two edges per hit take at most three times as long as placed (four times in
+    workgroups as large as the CU)."""
+    from paper_2508_07423_amd import etx
+    w = synth.C1.with_(k_max=2, gnn_steps=1)
+    few = [_event(490, i) for i in range(8)]
+    batch = {k: np.concatenate([few[i % 8][k] for i in range(4000)]) for k in few[0]}
+    batch["hit_off"] = np.arange(4001, dtype=np.int64) * 490
+    b = etx.to_device(batch)
+    p = etx.Pipeline(w, synth.xavier_weights(w))
+    ms = []
+    for place in (0, 1):
+        etx.etx_set_option(p.ctx, etx.ETX_OPT_CSC_PLACE, place)
+        ms.append(_csc_ms(etx, p, b))
+        _check_permutation(etx, p, b, batch)
+    p.close()
+    assert ms[0] < 3 * ms[1], ms
+
+
+# events on both sides of 1,024 hits and of four edges per hit, in batches above and below 1,024 hits per event
+@pytest.mark.parametrize("k_max", [1, 4, 5, 6])
+@pytest.mark.parametrize("extra", [[1023, 1024, 1025, 0, 63, 1, 16384], [4097] * 100])
+def test_small_events_walked(extra, k_max):
+    from paper_2508_07423_amd import etx
+    w = synth.C1.with_(k_max=k_max, gnn_steps=1)
+    batch = _batch(MANY + extra)
+    b = etx.to_device(batch)
+    p = etx.Pipeline(w, synth.xavier_weights(w))
+    etx.etx_set_option(p.ctx, etx.ETX_OPT_CSC_PLACE, 0)
+    p.run(b)
+    _check_permutation(etx, p, b, batch)
+    p.close()
