@@ -105,11 +105,14 @@ __device__ inline bool no_tiles(const GnnArgs& A, int64_t ntiles) {
 // written, and read again).  Measured at 10,000 uneven events of a trained
 // network, BF16 state, 1.9 edges per hit: edge encoder and edge steps 6.9 ->
 // 5.2 ms per pass, node steps 6.4 -> 6.1 ms.  With FP32 rows the second read
-// costs what the edge kernels gain (20.5 + 12.7 against 22.2 + 11.2 ms), and
-// long rows are read twice from memory, so FP32 state and more than kOwnRow
-// edges per hit keep the edge kernels' sums.  Both kernels decide on the same
-// two numbers.  Hidden size 32 only: at 64 the rows in flight do not fit the
-// registers beside the network's inputs.
+// costs what the edge kernels gain (20.5 + 12.7 against 22.2 + 11.2 ms), so FP32
+// state keeps the edge kernels' sums.  Long rows are read twice from memory, so
+// graphs of kOwnRow edges per hit and more do too.  That line is where trained
+// networks' graphs end, not where the gain does: 1,000 events at larger radii,
+// edge kernels' against own sums, whole pass, BF16 8.6 edges per hit 7.71 and 7.48
+// ms, 17 13.21 and 12.87; FP8 8.8 8.24 and 7.73, 17 14.11 and 13.35.  Both kernels
+// decide on the same two numbers.  Hidden size 32 only: at 64 the rows in flight do not fit the registers
+// beside the network's inputs.
 constexpr int kOwnRow = 6;
 template <int H, int P>
 constexpr bool kOwnForm = H == 32 && StorePrec<P>::value != P_F32;

@@ -100,11 +100,11 @@ struct etx_ctx {
   int radius_single = 1;           // radius graph: one selection pass + slot copy (0: count and emit passes)
   int fuse_messages = 0;           // message sums gathered inside the node-update kernel
   int radius_sort_min = 512;       // staged windows from this size on are sorted along their widest axis
-  int radius_fast = 0;             // select pass: 16-lane path for sources with few candidates
+  int radius_fast = 0;             // select pass: sources with few candidates, eight to a wave
   int radius_split = 0;            // radius search: small windows in a launch of its own with less LDS
   int xcd_map = 0;                 // tile and node kernels: contiguous work per XCD
   int edge_products = 0;           // 1: edge kernels form the node-product terms from gathered h rows
-  int csc_place = 1;               // short-row CSC placed by the whole block, then columns sorted
+  int csc_place = 1;               // 1: edges of short rows dropped into their columns, then ordered there; 0: rows walked
   int pf_features = 0;             // 1: prefilter inference also stores each candidate's features
   int compact_state = 0;           // BF16/FP8 runs: 1 keeps h, e in the operand format, 0 in FP32 (residual masters)
   std::vector<char> blob;          // the weight blob as given (for etx_save)

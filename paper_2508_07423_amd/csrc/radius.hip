@@ -274,7 +274,7 @@ __device__ inline void radius_unit(const RadiusArgs& A, float* lds, int ev, int 
     for (int c = threadIdx.x; c < nwin; c += kRadiusThreads) atomicAdd(&hist[cell_of(cemb[c * DP + axis])], 1);
     __syncthreads();
     if (wave == 0) {
-      // exclusive scan of the counts, four cells per lane
+      // exclusive scan of the counts, kCells / 64 cells per lane
       int v[kCells / 64], sum = 0;
 #pragma unroll
       for (int i = 0; i < kCells / 64; ++i) {
@@ -701,6 +701,11 @@ hipError_t launch_radius(const RunArgs& a, int mode, bool candidates) {
   // each of 2,900 units of small events 33 -> 64 us).  One trained full-size event
   // 60 -> 11 us; 20 uneven events of a trained network (two workgroups per unit ->
   // shared) 98 -> 47 us, of a dense one 298 -> 117.
+  // Workgroups per CU that may share (8 / 16 / 32, us): 20 dense uneven events 146 /
+  // 115 / 115, 100 small trained ones 30 / 30 / 34, 100 full-size trained ones 67 / 67
+  // / 73, but 100 dense uneven ones 920 / 916 / 692: sixteen lets no batch pay for
+  // workgroups without work.  Sources per sharing workgroup (units / 4, / 8, / 16):
+  // the 20 dense events 139 / 115 / 110, 20 trained ones 56 / 46 / 44.
   const int64_t units = a.hits.n_events * c.n_planes;
   auto parts = [&](int64_t per_cu) { return (int)std::max<int64_t>(1, std::min<int64_t>(8, per_cu * a.ctx->n_cu / units)); };
   A.part_sources = (int)std::max<int64_t>(1, std::min<int64_t>(128, units / 8));
@@ -712,7 +717,8 @@ hipError_t launch_radius(const RunArgs& a, int mode, bool candidates) {
   const bool split = a.ctx->radius_split && A.stage_window;
   const bool fast = A.fast && mode == R_SELECT;
   A.split = !split ? 0 : fast ? RadiusShape<8, R_SMALL_FAST>::cap : RadiusShape<8, R_SMALL>::cap;
-  // the small shapes' units are small: two workgroups per CU at most share them
+  // the small shapes' units are small: two workgroups per CU at most share them (one
+  // or four gave the same times)
 #define LAUNCH_R(M_, D_, F_)                                                                              \
   do {                                                                                                    \
     A.parts = parts(F_ == R_LARGE ? 16 : 2);                                                              \

@@ -292,7 +292,8 @@ __global__ __launch_bounds__(kHingeThreads) void k_hinge(HingeArgs A, int pass) 
   float n_gen = 0.f, n_fake = 0.f, loss = 0.f;
   float inv_g = 0.f, inv_f = 0.f;
   if (pass == 1) {
-    // the counts are whole numbers below 2^24: any order of addition gives them exactly
+    // whole numbers: exact while all pairs together are at most 2^24 (262,144 hits with
+    // 64 hard negatives each), rounded as any FP32 sum beyond, in a fixed order
     float cg = 0.f, cf = 0.f;
     for (int i = threadIdx.x; i < (int)gridDim.x; i += kHingeThreads) {
       cg += A.count_part[2 * i];
