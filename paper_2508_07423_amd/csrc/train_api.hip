@@ -25,6 +25,46 @@ namespace {
 
 size_t a256(size_t x) { return (x + 255) & ~size_t(255); }
 
+// Most partials of any number of rows up to `rows`.
+size_t most_chunks(int64_t rows) { return (size_t)std::min<int64_t>(rows, kTrainChunks); }
+
+// offsets (floats) of the parameter blocks in the blob payload
+struct ParamMap {
+  int64_t emb[8];           // embedding layer l
+  int64_t ne1, ne2, ee1, ee2, nn1[16], nn2[16], en1[16], en2[16], cls1, cls2, gnn_begin, total;
+};
+
+ParamMap param_map(const etx_config& c) {
+  ParamMap P{};
+  int64_t o = 0;
+  const int64_t W = c.emb_hidden, D = c.emb_dim, H = c.gnn_hidden;
+  for (int l = 0; l <= c.emb_layers && l < 8; ++l) {
+    const int64_t K = l == 0 ? 3 : W, M = l < c.emb_layers ? W : D;
+    P.emb[l] = o;
+    o += K * M + M;
+  }
+  P.gnn_begin = o;
+  auto take = [&](int64_t K, int64_t M) {
+    int64_t at = o;
+    o += K * M + M;
+    return at;
+  };
+  P.ne1 = take(3, H);
+  P.ne2 = take(H, H);
+  P.ee1 = take(2 * H, H);
+  P.ee2 = take(H, H);
+  for (int k = 0; k < c.gnn_steps; ++k) {
+    P.nn1[k] = take(3 * H, H);
+    P.nn2[k] = take(H, H);
+    P.en1[k] = take(3 * H, H);
+    P.en2[k] = take(H, H);
+  }
+  P.cls1 = take(H, H);
+  P.cls2 = take(H, 1);
+  P.total = o;
+  return P;
+}
+
 struct TrainLayout {
   // embedding
   size_t emb_z[4], de, g_gen, g_rnd, g_edge, counts;
@@ -67,10 +107,12 @@ TrainLayout train_layout(const etx_ctx* ctx, const WsLayout& L, int64_t n, int64
   T.dh = take(f * n * H);
   T.dmo = take(f * n * H);
   T.dmi = take(f * n * H);
-  // gradient partials: the embedding's over hits, the network's over hits and edges
-  const size_t P = blob_floats_of(c);
-  T.part = take(f * P * kTrainChunks);
-  T.grad = take(f * P);
+  // gradient partials: the embedding's over hits, the network's over hits and edges (at most one per pair of hits)
+  const ParamMap P = param_map(c);
+  const int64_t some = std::min<int64_t>(n, kTrainChunks);
+  T.part = take(f * most_chunks(std::max(some, std::min(E, some * (some - 1) / 2))) *
+                std::max(P.gnn_begin, P.total - P.gnn_begin));
+  T.grad = take(f * P.total);
   T.lpart = take(f * std::max(3 * kTrainChunks, kHingeBlocks));
   T.loss = take(f * 4);
   T.total = o;
@@ -105,47 +147,10 @@ TripLayout trip_layout(const etx_ctx* ctx, size_t base, int64_t n_events, int64_
   X.lab = take(T);
   X.dxa = take(f * T * H);
   X.dxb = take(f * T * H);
-  X.part = take(f * ETX_TRIPLET_NPARAM(H) * kTrainChunks);
+  X.part = take(f * ETX_TRIPLET_NPARAM(H) * most_chunks(tcap));
   X.tgrad = take(f * ETX_TRIPLET_NPARAM(H));
   X.total = o;
   return X;
-}
-
-// offsets (floats) of the parameter blocks in the blob payload
-struct ParamMap {
-  int64_t emb[8];           // embedding layer l
-  int64_t ne1, ne2, ee1, ee2, nn1[16], nn2[16], en1[16], en2[16], cls1, cls2, gnn_begin, total;
-};
-
-ParamMap param_map(const etx_config& c) {
-  ParamMap P{};
-  int64_t o = 0;
-  const int64_t W = c.emb_hidden, D = c.emb_dim, H = c.gnn_hidden;
-  for (int l = 0; l <= c.emb_layers && l < 8; ++l) {
-    const int64_t K = l == 0 ? 3 : W, M = l < c.emb_layers ? W : D;
-    P.emb[l] = o;
-    o += K * M + M;
-  }
-  P.gnn_begin = o;
-  auto take = [&](int64_t K, int64_t M) {
-    int64_t at = o;
-    o += K * M + M;
-    return at;
-  };
-  P.ne1 = take(3, H);
-  P.ne2 = take(H, H);
-  P.ee1 = take(2 * H, H);
-  P.ee2 = take(H, H);
-  for (int k = 0; k < c.gnn_steps; ++k) {
-    P.nn1[k] = take(3 * H, H);
-    P.nn2[k] = take(H, H);
-    P.en1[k] = take(3 * H, H);
-    P.en2[k] = take(H, H);
-  }
-  P.cls1 = take(H, H);
-  P.cls2 = take(H, 1);
-  P.total = o;
-  return P;
 }
 
 }  // namespace
